@@ -53,4 +53,8 @@ struct GemmGroup {
 };
 int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s);
 
+// The fp32 kernel (gemm_f32.hip): any layout, operand dtype and epilogue; the
+// problems of a group share ta and tb and are not empty.
+int gemm_f32(const GemmGroup& g, hipStream_t s);
+
 }  // namespace jg

@@ -14,8 +14,8 @@
 // then walked in GROUP_M-row bands, keeping the A rows and B columns a band
 // shares in one XCD's L2.
 //
-// Anything else (fp32 operands, contiguous dims not multiple of 8) takes a
-// plain LDS-tiled VALU kernel with fp32 accumulation.
+// Anything else (fp32 operands, contiguous dims not multiple of 8) takes the
+// fp32 kernel of gemm_f32.hip.
 #include <atomic>
 #include "gemm.h"
 #include <type_traits>
@@ -26,19 +26,6 @@ namespace jg {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__device__ inline void epi_apply(const Epi& e, int r, int c, float v) {
-  if (e.bias) v += ld_any(e.bias, e.bias_dt, c);
-  if (e.mode == EPI_GELU_FWD) {
-    st_any(e.aux, e.aux_dt, (size_t)r * e.ldaux + c, v);
-    v = gelu_tanh(v);
-  } else if (e.mode == EPI_GELU_BWD) {
-    v *= gelu_tanh_grad(ld_any(e.aux, e.aux_dt, (size_t)r * e.ldaux + c));
-  }
-  const size_t idx = (size_t)r * e.ldc + c;
-  if (e.beta != 0.f) v += e.beta * ld_any(e.C, e.c_dt, idx);
-  st_any(e.C, e.c_dt, idx, v);
-}
 
 __device__ inline int xcd_remap(int b, int total) {
   const int per = total / 8, rem = total % 8;
@@ -1027,53 +1014,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
   dtl_epilogue<BM, BN, WM, WN, EK>(g, acc, m0, n0, T);
 }
 
-// ---------------------------------------------------------------- VALU GEMM
-// 64x64 tile, 256 threads, 4x4 outputs per thread, fp32 accumulation, any
-// layout and operand dtype.
-__global__ __launch_bounds__(256) void gemm_valu_kernel(GemmArgs g) {
-  constexpr int T = 64, KT = 16;
-  __shared__ float As[KT][T + 1];
-  __shared__ float Bs[KT][T + 1];
-  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += KT) {
-    for (int i = threadIdx.x; i < KT * T; i += 256) {
-      const int kk = i / T, mm = i % T;
-      const int k = k0 + kk;
-      const int m = m0 + mm, n = n0 + mm;
-      float a = 0.f, b = 0.f;
-      if (k < g.K && m < g.M)
-        a = ld_any(g.A, g.a_dt, g.ta ? (size_t)k * g.lda + m : (size_t)m * g.lda + k);
-      if (k < g.K && n < g.N)
-        b = ld_any(g.B, g.b_dt, g.tb ? (size_t)k * g.ldb + n : (size_t)n * g.ldb + k);
-      As[kk][mm] = a;
-      Bs[kk][mm] = b;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KT; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty + 16 * i, n = n0 + tx + 16 * j;
-      if (m < g.M && n < g.N) epi_apply(g.epi, m, n, acc[i][j]);
-    }
-}
-
 // ------------------------------------------------------------------ launch
 static GemmGroup single(const GemmArgs& g) {
   GemmGroup r;
@@ -1311,12 +1251,9 @@ static int gemm_launch(const GemmArgs& g, hipStream_t s) {
     if (g.ta && g.tb) return launch_kind<true, true>(g, s, cfg, ek);
     return launch_kind<true, false>(g, s, cfg, ek);
   }
-  // the VALU kernel also covers an empty contraction (K = 0): it still
+  // the fp32 kernel also covers an empty contraction (K = 0): it still
   // applies the epilogue (bias, beta)
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-  launch(gemm_valu_kernel, grid, dim3(256), 0u, s, g);
-  JG_CHECK_LAUNCH("gemm_valu");
-  return 0;
+  return gemm_f32(single(g), s);
 }
 
 template <bool TA, int EK>
@@ -1334,13 +1271,16 @@ static int launch_fwd_group(const GemmGroup& g, hipStream_t s) {
 
 int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   // one grouped launch when both products take the same kernel: the
-  // direct-to-LDS kernel (k-strided B: input and weight gradients) or the
+  // direct-to-LDS kernel (k-strided B: input and weight gradients), the
   // register-staged one (forward products, K a multiple of its 64-deep tile)
-  const int ek = (a.M > 0 && a.N > 0 && b.M > 0 && b.N > 0 && a.A && a.B && a.epi.C && b.A && b.B && b.epi.C)
-                     ? mfma_kind(a) : -1;
-  const bool same = ek >= 0 && mfma_kind(b) == ek && a.ta == b.ta && a.tb == b.tb;
+  // or the fp32 one
+  const bool whole = a.M > 0 && a.N > 0 && b.M > 0 && b.N > 0 && a.K >= 0 && b.K >= 0 && a.A && a.B && a.epi.C && b.A &&
+                     b.B && b.epi.C;
+  const int ek = whole ? mfma_kind(a) : -1, ekb = whole ? mfma_kind(b) : -1;
+  const bool alike = whole && a.ta == b.ta && a.tb == b.tb, same = alike && ek >= 0 && ekb == ek;
+  const bool f32 = alike && ek < 0 && ekb < 0;
   const bool fwd = same && !a.ta && !a.tb && a.K % 64 == 0 && b.K % 64 == 0;
-  const bool grouped = fwd || (same && a.tb && dtl_fits(a) && dtl_fits(b));
+  const bool grouped = f32 || fwd || (same && a.tb && dtl_fits(a) && dtl_fits(b));
   if (!grouped) {
     int rc = gemm(a, s);
     return rc ? rc : gemm(b, s);
@@ -1352,6 +1292,11 @@ int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   g.p[1] = b.K > a.K ? a : b;
   const int pi = prof_begin(prof_class(a));
   int rc;
+  if (f32) {
+    rc = gemm_f32(g, s);
+    prof_end(pi, 2.0 * ((double)a.M * a.N * a.K + (double)b.M * b.N * b.K));
+    return rc;
+  }
   if (fwd) {
     switch (ek) {
 #define JG_FWD(E) case E: rc = launch_fwd_group<E>(g, s); break;

@@ -1,0 +1,56 @@
+"""GPU parity of the kernels chosen by size and type, at the sizes where their
+rules and tile edges lie.  Whole passes (pair forward and JAGG group backward)
+against the oracle in fp64; bars as in test_gpu_parity: fp32 1e-4, bf16 2e-2,
+globally and per tensor."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_17572_amd as pk
+import synth
+from harness import Case, compare_grads, rel_l2, rounded, to_dev
+from oracle import mmdit
+
+pytestmark = pytest.mark.gpu
+
+
+def block(heads, head_dim, n_txt, lat_h, lat_w, act=pk.F32, **over):
+    d = heads * head_dim
+    k = dict(n_double=1, n_single=0, hidden=d, heads=heads, head_dim=head_dim, mlp_hidden=4 * d, in_ch=16, patch=2,
+             lat_h=lat_h, lat_w=lat_w, n_txt=n_txt, txt_dim=d, t_freq_dim=256, block_only=1, act_dtype=act,
+             grad_dtype=pk.F32)
+    k.update(over)
+    return pk.Config(**k)
+
+
+def check_pass(c, B, W, tol):
+    cs = Case(c, B=B, W=W)
+    eg, worst = compare_grads(cs, cs.gpu_jagg(), cs.oracle_jagg(), tol, report=True)
+    print(f"rel L2 {eg:.2e}, worst tensor {worst}", flush=True)
+
+
+# fp32 products: 64 x 64 tiles from 480 of them on (4 x 517 rows: 528 tiles for the MLP's first layer), 32 x 32 tiles
+# below, ragged rows in both; rows that are not 16-byte aligned (3-wide patches, 30-wide text embeddings)
+@pytest.mark.parametrize("c,B", [
+    (block(4, 64, 77, 40, 44), 2),
+    (block(3, 16, 5, 6, 10), 1),
+    (block(2, 32, 7, 6, 5, block_only=0, in_ch=3, patch=1, txt_dim=30, n_single=1), 1),
+], ids=["tiles64", "tiles32", "unaligned"])
+def test_fp32_products(c, B):
+    check_pass(c, B, 3, 1e-4)
+
+
+# bf16 operands whose rows are not 16-byte aligned, at 64 x 64 tiles of the fp32 kernel (32 x 32 of them)
+def test_unaligned_bf16_products():
+    rows, n_out, n_in = 2001, 2004, 516
+    dY = rounded(synth.normal((rows, n_out), 1), torch.bfloat16)
+    X = rounded(synth.normal((rows, n_in), 2), torch.bfloat16)
+    W = rounded(synth.normal((n_out, n_in), 3, scale=0.02), torch.bfloat16)
+    ctx = pk.Context(pk.config("tiny"))
+    dX = torch.empty(rows, n_in, dtype=torch.float32, device="cuda")
+    ctx.linear_grad(pk.DGRAD, to_dev(dY, torch.bfloat16), to_dev(W, torch.bfloat16), dX)
+    dW = torch.ones(n_out, n_in, dtype=torch.float32, device="cuda")
+    ctx.linear_grad(pk.WGRAD, to_dev(dY, torch.bfloat16), to_dev(X, torch.bfloat16), dW, beta=1.0)
+    # fp32 sums of exact products: 2000 terms, relative error below sqrt(2000) 2^-24 = 3e-6
+    assert rel_l2(dX.double().cpu().numpy(), dY @ W) <= 1e-5
+    assert rel_l2(dW.double().cpu().numpy(), 1.0 + mmdit.wgrad(dY, X)) <= 1e-5
