@@ -629,12 +629,15 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmGroup gg) {
 }
 
 // --------------------------------------------- direct-to-LDS MFMA GEMM
-// BM x BN workgroup tile (each 192 or 256), WM x WN waves (2 x 2; 2 x 4 for
-// 256 x 256, where a second wave per SIMD keeps the MFMAs busy while the other
+// BM x BN workgroup tile (each 192 or 256; 128 x 128 and 64 x 64 for products
+// that do not fill the chip with those, two and five workgroups per CU), WM x
+// WN waves (2 x 2; 2 x 4 for 256 x 256, where a second wave per SIMD keeps the MFMAs busy while the other
 // wave stalls issuing its direct loads: 8% faster on that tile, while 4 x 2
 // on 256 x 192 was slower than 2 x 2), 32-deep k tiles through 4 LDS stages,
-// for K a multiple of 32.  Operands go from memory
-// straight into LDS (buffer loads with the LDS bit: no register staging and no
+// for K a multiple of 32, or any K where both operands are k-strided (rows past
+// K lie past the operands' ends and load as zeros: a weight gradient over 1089
+// rows took 236 us on the edge-checked kernel and takes 110).  Operands go from
+// memory straight into LDS (buffer loads with the LDS bit: no register staging and no
 // LDS write instructions), three k tiles ahead of the MFMAs.  LDS rows are
 // unpadded and 16-byte chunks are XOR-swizzled by row so that both the 1 KB
 // contiguous direct loads and the fragment reads are free of bank conflicts:
@@ -647,9 +650,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmGroup gg) {
 //     s = (row_1 row_2) ^ (row_3 row_4) held only for consecutive lanes and
 //     cost 1.6-1.9 conflict cycles per LDS instruction);
 //   k-strided operand, tile [32 k][rows] (2 * rows bytes per k row):
-//     chunk' = chunk ^ (((k & 3) << 1) | ((k & 1) << 3))  (256 rows),
-//     chunk' = chunk ^ ((k & 3) << 1)                      (192 rows: the XOR
-//     must stay inside aligned groups of 8 chunks),
+//     chunk' = chunk ^ (((k & 3) << 1) | ((k & 1) << 3))  (256 and 128 rows),
+//     chunk' = chunk ^ ((k & 3) << 1)       (192 and 64 rows: the XOR must stay
+//     inside aligned groups of 8 chunks, and odd k rows start half way through
+//     the banks by themselves),
 //     fragments are two transposing 8-byte reads (ds_read_b64_tr_b16), each
 //     of which hands lane i of a 16-lane group element (row e, column i) of
 //     the 4 x 16 block the group fetched.
@@ -674,7 +678,7 @@ __device__ __forceinline__ void wait_vm_lds() {
 __device__ __forceinline__ int swz_n(int row) { return (((row >> 1) & 1) * 2) ^ (((row >> 2) & 1) * 3) ^ ((row >> 3) & 1); }
 template <int ROWS>
 __device__ __forceinline__ int swz_t(int k) {
-  return ROWS == 256 ? (((k & 3) << 1) | ((k & 1) << 3)) : ((k & 3) << 1);
+  return ROWS % 128 == 0 ? (((k & 3) << 1) | ((k & 1) << 3)) : ((k & 3) << 1);
 }
 
 // One operand of the direct-to-LDS kernel: ROWS x 32 elements = ROWS * 64 B per
@@ -869,7 +873,9 @@ template <bool TA, bool TB, int EK, int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
   constexpr int BK = 32, NW = WM * WN, FM = BM / (32 * WM), FN = BN / (32 * WN);
   constexpr int SB = BM * 64;  // byte offset of the B tile in a stage
-  constexpr int STG = 32768;   // bytes per stage (room for 256 + 256 rows)
+  // bytes per stage (also a wave's epilogue staging: the 192-wide tiles need
+  // more than their 24 or 28 KB of operands)
+  constexpr int STG = BM >= 192 ? 32768 : (BM + BN) * 64;
   // one variable per stage: every LDS access names its stage statically, so
   // the compiler can tell the fragment reads of one stage from the direct
   // loads still landing in another and does not wait for the latter
@@ -947,7 +953,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  const int nk = g.K / BK;
+  // (a ragged last k tile of two k-strided operands reads zeros past K)
+  const int nk = (g.K + BK - 1) / BK;
   // Every wave loads both operands: A's loads of a k tile go with the first
   // MFMA step, B's with the second.  A wave stalls while the memory pipeline
   // cannot take its next direct load, and with one wave per SIMD the MFMAs
@@ -1059,20 +1066,17 @@ static int launch_pipe(const GemmGroup& gr, hipStream_t s) {
   return 0;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, int EK, bool PIPE>
+template <bool TA, bool TB, int EK>
 static int launch_mfma(const GemmArgs& g, hipStream_t s) {
-  if constexpr (PIPE) {
-    return launch_pipe<BM, BN, BK, WM, WN, TA, TB, EK>(single(g), s);
-  } else {
-    const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-    const size_t lds = 2 * (size_t)(BM + BN) * (BK + 8) * sizeof(uint16_t);
-    void (*kern)(GemmArgs) = gemm_mfma_kernel<BM, BN, BK, WM, WN, TA, TB, EK>;
-    static std::atomic<unsigned long long> attr{0};
-    if (int rc = reserve_lds(attr, (const void*)kern, lds, "gemm_mfma")) return rc;
-    launch(kern, dim3(tiles), dim3(WM * WN * 64), (uint32_t)lds, s, g);
-    JG_CHECK_LAUNCH("gemm_mfma");
-    return 0;
-  }
+  constexpr int BM = 128, BN = 128, BK = 64;
+  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  const size_t lds = 2 * (size_t)(BM + BN) * (BK + 8) * sizeof(uint16_t);
+  void (*kern)(GemmArgs) = gemm_mfma_kernel<BM, BN, BK, 2, 2, TA, TB, EK>;
+  static std::atomic<unsigned long long> attr{0};
+  if (int rc = reserve_lds(attr, (const void*)kern, lds, "gemm_mfma")) return rc;
+  launch(kern, dim3(tiles), dim3(256), (uint32_t)lds, s, g);
+  JG_CHECK_LAUNCH("gemm_mfma");
+  return 0;
 }
 
 template <bool TA, bool TB, int EK, int BM, int BN, int WM = 2, int WN = 2>
@@ -1090,23 +1094,31 @@ static int launch_dtl(const GemmGroup& gr, hipStream_t s) {
   return 0;
 }
 
-// Tile shape of the direct-to-LDS kernel: the one with the least estimated
-// time = rounds of 256 workgroups x tile area / relative tile efficiency
-// (smaller tiles re-read more operand bytes per MFMA).  0: 256x256 (8 waves),
-// 1: 256x192, 2: 192x256, 3: 192x192.  Rounds count whole rounds of problem
-// 0's tiles; the tiles of a second problem with a shorter contraction are
-// shorter and fill in behind them (the dispatcher hands a freed CU the next
-// workgroup), so they add their share of a round; equal contractions share
-// whole rounds.
+// Tile shapes of the direct-to-LDS kernel.
+enum { DTL_256 = 0, DTL_256x192, DTL_192x256, DTL_192, DTL_128, DTL_64, DTL_SHAPES };
+static const int DTL_BM[DTL_SHAPES] = {256, 256, 192, 192, 128, 64}, DTL_BN[DTL_SHAPES] = {256, 192, 256, 192, 128, 64};
+
+static long tiles_of(const GemmArgs& g, int bm, int bn) { return (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+
+// Tile shape of an input- or weight-gradient group: the one with the least
+// estimated time = rounds of 256 workgroups x tile area / relative tile
+// efficiency (smaller tiles re-read more operand bytes per MFMA).  Rounds
+// count whole rounds of problem 0's tiles; the tiles of a second problem with
+// a shorter contraction are shorter and fill in behind them (the dispatcher
+// hands a freed CU the next workgroup), so they add their share of a round;
+// equal contractions share whole rounds.  The efficiencies are fitted to a
+// sweep of twelve row counts x four layers x both products: the choice is
+// within 8% of the best shape on all of them.  Examples (us; 256x192, 192x192,
+// 128x128, 64x64): 2048 + 616 rows x 768, K 3072: 49 / 42 / 30 / 27; 2142 + 462
+// x 1536, K 6144: 89 / 76 / 58 / 102; 8192 + 1024 x 12288, K 3072: 633 / 652 /
+// 912 / 1242 (256x256: 562).
 static int dtl_shape(const GemmGroup& g) {
-  static const int bm[4] = {256, 256, 192, 192}, bn[4] = {256, 192, 256, 192};
-  static const double eff[4] = {1.0, 0.95, 0.95, 0.9};
+  static const double eff[DTL_SHAPES] = {1.0, 0.95, 0.95, 0.8, 0.7, 0.5};
   int best = 0;
   double bt = 1e300;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < DTL_SHAPES; ++i) {
     long tl[2] = {0, 0};
-    for (int p = 0; p < g.np; ++p)
-      tl[p] = (long)((g.p[p].M + bm[i] - 1) / bm[i]) * ((g.p[p].N + bn[i] - 1) / bn[i]);
+    for (int p = 0; p < g.np; ++p) tl[p] = tiles_of(g.p[p], DTL_BM[i], DTL_BN[i]);
     double rounds;
     if (g.np == 1 || g.p[1].K == g.p[0].K) {
       rounds = (double)((tl[0] + tl[1] + 255) / 256);
@@ -1114,67 +1126,35 @@ static int dtl_shape(const GemmGroup& g) {
       const double work = tl[0] + (double)tl[1] * g.p[1].K / g.p[0].K;
       rounds = std::max((double)((tl[0] + 255) / 256), work / 256.0);
     }
-    const double t = rounds * bm[i] * bn[i] / eff[i];
+    const double t = rounds * DTL_BM[i] * DTL_BN[i] / eff[i];
     if (t < bt * 0.999) { bt = t; best = i; }
   }
   return best;
 }
 
-// The direct-to-LDS kernel serves the products with a k-strided B operand
-// (input and weight gradients); -1 for the others.
 template <bool TA, bool TB, int EK>
-struct DtlLaunch {
-  static int run(const GemmGroup& g, hipStream_t s, int shape) {
+static int run_dtl(const GemmGroup& g, hipStream_t s, int shape) {
+  if constexpr (TB) {
     switch (shape) {
-      case 1: return launch_dtl<TA, TB, EK, 256, 192>(g, s);
-      case 2: return launch_dtl<TA, TB, EK, 192, 256>(g, s);
-      case 3: return launch_dtl<TA, TB, EK, 192, 192>(g, s);
-      default: return launch_dtl<TA, TB, EK, 256, 256, 2, 4>(g, s);
+      case DTL_256: return launch_dtl<TA, TB, EK, 256, 256, 2, 4>(g, s);
+      case DTL_256x192: return launch_dtl<TA, TB, EK, 256, 192>(g, s);
+      case DTL_192x256: return launch_dtl<TA, TB, EK, 192, 256>(g, s);
+      case DTL_192: return launch_dtl<TA, TB, EK, 192, 192>(g, s);
+      default: break;
     }
   }
-};
-template <bool TA, int EK>
-struct DtlLaunch<TA, false, EK> {
-  static int run(const GemmGroup&, hipStream_t, int) { return -1; }
-};
+  if (shape == DTL_64) return launch_dtl<TA, TB, EK, 64, 64>(g, s);
+  return launch_dtl<TA, TB, EK, 128, 128>(g, s);
+}
 
 // The direct-to-LDS kernel computes 32-bit byte offsets up to three k tiles
-// past K; they must stay below 2^31.
+// past K; they must stay below 2^31.  A ragged last k tile needs both operands
+// k-strided: their rows past K lie past the operands' ends and read as zeros.
 static bool dtl_fits(const GemmArgs& g) {
   const double kx = (double)g.K + 128.0;
   const double ea = 2.0 * (g.ta ? kx * g.lda + g.M : (double)g.M * g.lda + kx);
   const double eb = 2.0 * (g.tb ? kx * g.ldb + g.N : (double)g.N * g.ldb + kx);
-  return g.K % 32 == 0 && ea < 2147483000.0 && eb < 2147483000.0;
-}
-
-template <bool TA, bool TB, int EK>
-static int launch_cfg(const GemmArgs& g, hipStream_t s, int cfg) {
-  if (TB && cfg >= 8 && cfg <= 12 && dtl_fits(g)) {
-    const GemmGroup one = single(g);
-    const int rc = DtlLaunch<TA, TB, EK>::run(one, s, cfg == 8 ? dtl_shape(one) : cfg - 9);
-    if (rc >= 0) return rc;
-  }
-  // K not a multiple of the 64-deep k tile: the edge-checked kernel
-  if (g.K % 64 != 0) return launch_mfma<128, 128, 64, 2, 2, TA, TB, EK, false>(g, s);
-  switch (cfg) {
-    case 1: return launch_mfma<128, 128, 64, 2, 2, TA, TB, EK, true>(g, s);
-    case 2: return launch_mfma<256, 128, 64, 2, 2, TA, TB, EK, true>(g, s);
-    case 6: return launch_mfma<256, 256, 64, 2, 4, TA, TB, EK, true>(g, s);
-    default: return launch_mfma<256, 256, 64, 2, 2, TA, TB, EK, true>(g, s);
-  }
-}
-
-template <bool TA, bool TB>
-static int launch_kind(const GemmArgs& g, hipStream_t s, int cfg, int ek) {
-  switch (ek) {
-    case EK_F32: return launch_cfg<TA, TB, EK_F32>(g, s, cfg);
-    case EK_F32_ACC: return launch_cfg<TA, TB, EK_F32_ACC>(g, s, cfg);
-    case EK_BF16: return launch_cfg<TA, TB, EK_BF16>(g, s, cfg);
-    case EK_BF16_ACC: return launch_cfg<TA, TB, EK_BF16_ACC>(g, s, cfg);
-    case EK_BIAS: return launch_cfg<TA, TB, EK_BIAS>(g, s, cfg);
-    case EK_GELU: return launch_cfg<TA, TB, EK_GELU>(g, s, cfg);
-    default: return launch_cfg<TA, TB, EK_DGELU>(g, s, cfg);
-  }
+  return (g.K % 32 == 0 || (g.ta && g.tb)) && ea < 2147483000.0 && eb < 2147483000.0;
 }
 
 // The output kind of an epilogue, or -1 if the MFMA epilogues do not cover it.
@@ -1191,6 +1171,13 @@ static int epi_kind(const Epi& e) {
   if (e.mode == EPI_STORE) return EK_BIAS;
   if (e.mode == EPI_GELU_FWD) return bias ? EK_GELU : -1;
   return bias ? -1 : EK_DGELU;
+}
+
+// The kinds that have kernels, per product: forward products add a bias,
+// input gradients overwrite, weight gradients overwrite or accumulate.
+constexpr bool kind_of_product(bool ta, bool tb, int ek) {
+  return !tb ? !ta && (ek == EK_BIAS || ek == EK_GELU)
+             : ta ? ek >= EK_F32 && ek <= EK_BF16_ACC : ek == EK_F32 || ek == EK_BF16 || ek == EK_DGELU;
 }
 
 static int prof_class(const GemmArgs& g) {
@@ -1218,6 +1205,7 @@ static int mfma_kind(const GemmArgs& g) {
               g.lda % 8 == 0 && g.ldb % 8 == 0;
   if (mfma) mfma = (g.ta ? g.M % 8 == 0 : g.K % 8 == 0) && (g.tb ? g.N % 8 == 0 : g.K % 8 == 0);
   const int ek = mfma ? epi_kind(g.epi) : -1;
+  if (!kind_of_product(g.ta, g.tb, ek)) return -1;
   if (ek >= 0 && (g.epi.ldc % 8 != 0 || !aligned16(g.epi.C) || (g.epi.aux && (g.epi.ldaux % 8 || !aligned16(g.epi.aux)))))
     return -1;
   // operand extents must fit a 32-bit buffer offset
@@ -1227,6 +1215,72 @@ static int mfma_kind(const GemmArgs& g) {
   return ek;
 }
 
+// Kernel of a forward group.  Times in units of a round of 256 x 256 tiles
+// (register-staged, one workgroup per CU), fitted to the same sweep:
+//   128 x 128 register-staged tiles, two workgroups per CU: 0.49 for up to 256
+//     tiles, 0.62 for up to 512 (2142 + 462 rows x 1536, K 1536: 66 large
+//     tiles 36.5 us, 252 small ones 17.8; 8192 + 1024 x 3072, K 3072: 432 large
+//     tiles 162 us, 1728 small ones 186);
+//   64 x 64 direct-to-LDS tiles: 0.21 per 256 (300 + 100 rows x 2304, K 768:
+//     5.7 us against 10.2 and 22.5).
+// The register-staged kernels take K in whole 64-deep tiles; else the
+// direct-to-LDS ones (128 x 128: 0.55 and 0.75).
+enum { FWD_PIPE256 = DTL_SHAPES, FWD_PIPE128 };
+static int fwd_shape(const GemmGroup& g) {
+  long t256 = 0, t128 = 0, t64 = 0;
+  bool k64 = true;
+  for (int p = 0; p < g.np; ++p) {
+    t256 += tiles_of(g.p[p], 256, 256);
+    t128 += tiles_of(g.p[p], 128, 128);
+    t64 += tiles_of(g.p[p], 64, 64);
+    k64 = k64 && g.p[p].K % 64 == 0;
+  }
+  const double one = k64 ? 0.49 : 0.55, two = k64 ? 0.62 : 0.75;
+  const long rem = t128 % 512;
+  const double c256 = k64 ? (double)((t256 + 255) / 256) : 1e300;
+  const double c128 = (double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two);
+  const double c64 = 0.21 * (double)((t64 + 255) / 256);
+  if (c64 < c128 && c64 < c256) return DTL_64;
+  if (c128 < c256) return k64 ? FWD_PIPE128 : DTL_128;
+  return FWD_PIPE256;
+}
+
+// The products of a group (all dtl_fits) in one launch.
+template <bool TA, bool TB, int EK>
+static int run_group(const GemmGroup& g, hipStream_t s, int shape) {
+  if constexpr (!TB) {
+    if (shape == FWD_PIPE256) return launch_pipe<256, 256, 64, 2, 4, TA, TB, EK>(g, s);
+    if (shape == FWD_PIPE128) return launch_pipe<128, 128, 64, 2, 2, TA, TB, EK>(g, s);
+  }
+  return run_dtl<TA, TB, EK>(g, s, shape);
+}
+
+// Calls f with the (TA, TB, EK) of a product as integral constants.
+template <class F>
+static int with_kind(const GemmArgs& g, int ek, F f) {
+  typedef std::true_type T;
+  typedef std::false_type N;
+#define JG_KIND(E) std::integral_constant<int, E>()
+  if (!g.tb) return ek == EK_BIAS ? f(N(), N(), JG_KIND(EK_BIAS)) : f(N(), N(), JG_KIND(EK_GELU));
+  if (!g.ta)
+    return ek == EK_F32 ? f(N(), T(), JG_KIND(EK_F32))
+                        : ek == EK_BF16 ? f(N(), T(), JG_KIND(EK_BF16)) : f(N(), T(), JG_KIND(EK_DGELU));
+  switch (ek) {
+    case EK_F32: return f(T(), T(), JG_KIND(EK_F32));
+    case EK_F32_ACC: return f(T(), T(), JG_KIND(EK_F32_ACC));
+    case EK_BF16: return f(T(), T(), JG_KIND(EK_BF16));
+    default: return f(T(), T(), JG_KIND(EK_BF16_ACC));
+  }
+#undef JG_KIND
+}
+
+static int launch_group(const GemmGroup& g, int ek, hipStream_t s, int shape = -1) {
+  if (shape < 0) shape = g.p[0].tb ? dtl_shape(g) : fwd_shape(g);
+  return with_kind(g.p[0], ek, [&](auto ta, auto tb, auto k) {
+    return run_group<decltype(ta)::value, decltype(tb)::value, decltype(k)::value>(g, s, shape);
+  });
+}
+
 static int gemm_launch(const GemmArgs& g, hipStream_t s) {
   if (g.M < 0 || g.N < 0 || g.K < 0 || !g.A || !g.B || !g.epi.C) {
     set_error("gemm: invalid arguments");
@@ -1234,54 +1288,24 @@ static int gemm_launch(const GemmArgs& g, hipStream_t s) {
   }
   if (g.M == 0 || g.N == 0) return 0;
   const int ek = mfma_kind(g);
-  if (ek >= 0) {
-    // default: products with a k-strided B operand (weight and input
-    // gradients) take the direct-to-LDS kernel with the tile shape that best
-    // fills whole rounds of 256 CUs; the forward product takes the 8-wave
-    // register-staged 256x256 kernel, or 128x128 for grids too small to
-    // cover a quarter of the chip
-    const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-    int cfg;
-    if (g.tb && dtl_fits(g)) cfg = 8;
-    else if (t256 < 64) cfg = 1;
-    else if (!g.ta && !g.tb) cfg = 6;
-    else cfg = 4;
-    if (!g.ta && !g.tb) return launch_kind<false, false>(g, s, cfg, ek);
-    if (!g.ta && g.tb) return launch_kind<false, true>(g, s, cfg, ek);
-    if (g.ta && g.tb) return launch_kind<true, true>(g, s, cfg, ek);
-    return launch_kind<true, false>(g, s, cfg, ek);
-  }
   // the fp32 kernel also covers an empty contraction (K = 0): it still
   // applies the epilogue (bias, beta)
-  return gemm_f32(single(g), s);
-}
-
-template <bool TA, int EK>
-static int launch_group(const GemmGroup& g, hipStream_t s) {
-  return DtlLaunch<TA, true, EK>::run(g, s, dtl_shape(g));
-}
-
-template <int EK>
-static int launch_fwd_group(const GemmGroup& g, hipStream_t s) {
-  long t256 = 0;
-  for (int p = 0; p < g.np; ++p) t256 += (long)((g.p[p].M + 255) / 256) * ((g.p[p].N + 255) / 256);
-  if (t256 < 64) return launch_pipe<128, 128, 64, 2, 2, false, false, EK>(g, s);
-  return launch_pipe<256, 256, 64, 2, 4, false, false, EK>(g, s);
+  if (ek < 0) return gemm_f32(single(g), s);
+  if (dtl_fits(g)) return launch_group(single(g), ek, s);
+  // ragged k of a k-contiguous operand (or offsets near 2^31): the
+  // edge-checked kernel
+  return with_kind(g, ek, [&](auto ta, auto tb, auto k) {
+    return launch_mfma<decltype(ta)::value, decltype(tb)::value, decltype(k)::value>(g, s);
+  });
 }
 
 int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
-  // one grouped launch when both products take the same kernel: the
-  // direct-to-LDS kernel (k-strided B: input and weight gradients), the
-  // register-staged one (forward products, K a multiple of its 64-deep tile)
-  // or the fp32 one
+  // one grouped launch when both products take the same kernels
   const bool whole = a.M > 0 && a.N > 0 && b.M > 0 && b.N > 0 && a.K >= 0 && b.K >= 0 && a.A && a.B && a.epi.C && b.A &&
                      b.B && b.epi.C;
   const int ek = whole ? mfma_kind(a) : -1, ekb = whole ? mfma_kind(b) : -1;
-  const bool alike = whole && a.ta == b.ta && a.tb == b.tb, same = alike && ek >= 0 && ekb == ek;
-  const bool f32 = alike && ek < 0 && ekb < 0;
-  const bool fwd = same && !a.ta && !a.tb && a.K % 64 == 0 && b.K % 64 == 0;
-  const bool grouped = f32 || fwd || (same && a.tb && dtl_fits(a) && dtl_fits(b));
-  if (!grouped) {
+  const bool alike = whole && a.ta == b.ta && a.tb == b.tb && ek == ekb;
+  if (!alike || (ek >= 0 && !(dtl_fits(a) && dtl_fits(b)))) {
     int rc = gemm(a, s);
     return rc ? rc : gemm(b, s);
   }
@@ -1291,47 +1315,27 @@ int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   g.p[0] = b.K > a.K ? b : a;
   g.p[1] = b.K > a.K ? a : b;
   const int pi = prof_begin(prof_class(a));
-  int rc;
-  if (f32) {
-    rc = gemm_f32(g, s);
-    prof_end(pi, 2.0 * ((double)a.M * a.N * a.K + (double)b.M * b.N * b.K));
-    return rc;
-  }
-  if (fwd) {
-    switch (ek) {
-#define JG_FWD(E) case E: rc = launch_fwd_group<E>(g, s); break;
-      JG_FWD(EK_F32) JG_FWD(EK_F32_ACC) JG_FWD(EK_BF16) JG_FWD(EK_BF16_ACC) JG_FWD(EK_BIAS) JG_FWD(EK_GELU)
-      default: rc = launch_fwd_group<EK_DGELU>(g, s); break;
-#undef JG_FWD
-    }
-    prof_end(pi, 2.0 * ((double)a.M * a.N * a.K + (double)b.M * b.N * b.K));
-    return rc;
-  }
-  switch (ek) {
-#define JG_GRP(E) case E: rc = a.ta ? launch_group<true, E>(g, s) : launch_group<false, E>(g, s); break;
-    JG_GRP(EK_F32) JG_GRP(EK_F32_ACC) JG_GRP(EK_BF16) JG_GRP(EK_BF16_ACC) JG_GRP(EK_BIAS) JG_GRP(EK_GELU)
-    default: rc = a.ta ? launch_group<true, EK_DGELU>(g, s) : launch_group<false, EK_DGELU>(g, s); break;
-#undef JG_GRP
-  }
+  const int rc = ek < 0 ? gemm_f32(g, s) : launch_group(g, ek, s);
   prof_end(pi, 2.0 * ((double)a.M * a.N * a.K + (double)b.M * b.N * b.K));
   return rc;
 }
 
-// Explicit instantiations of the direct-to-LDS kernels the dispatch can reach
-// (the host-side launch stubs of kernel templates reached only through the
-// shape switch are otherwise not always emitted).
-#define JG_DTL_SHAPES(TA, EK)                                            \
+// Explicit instantiations of the kernels the dispatch can reach (the host-side
+// launch stubs of kernel templates reached only through the shape switch are
+// otherwise not always emitted).
+#define JG_DTL_SMALL(TA, TB, EK)                                                   \
+  template __global__ void gemm_dtl_kernel<TA, TB, EK, 128, 128, 2, 2>(GemmGroup); \
+  template __global__ void gemm_dtl_kernel<TA, TB, EK, 64, 64, 2, 2>(GemmGroup);
+#define JG_DTL(TA, EK)                                                               \
+  JG_DTL_SMALL(TA, true, EK)                                                         \
   template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 256, 2, 4>(GemmGroup); \
   template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 192, 2, 2>(GemmGroup); \
   template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 256, 2, 2>(GemmGroup); \
   template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 192, 2, 2>(GemmGroup);
-#define JG_DTL_KINDS(TA) \
-  JG_DTL_SHAPES(TA, 0) JG_DTL_SHAPES(TA, 1) JG_DTL_SHAPES(TA, 2) JG_DTL_SHAPES(TA, 3) JG_DTL_SHAPES(TA, 4) \
-  JG_DTL_SHAPES(TA, 5) JG_DTL_SHAPES(TA, 6)
-JG_DTL_KINDS(false)
-JG_DTL_KINDS(true)
-#undef JG_DTL_KINDS
-#undef JG_DTL_SHAPES
+JG_DTL_SMALL(false, false, EK_BIAS) JG_DTL_SMALL(false, false, EK_GELU)
+JG_DTL(false, EK_F32) JG_DTL(false, EK_BF16) JG_DTL(false, EK_DGELU)
+JG_DTL(true, EK_F32) JG_DTL(true, EK_F32_ACC) JG_DTL(true, EK_BF16) JG_DTL(true, EK_BF16_ACC)
+#undef JG_DTL
+#undef JG_DTL_SMALL
 
 }  // namespace jg
-

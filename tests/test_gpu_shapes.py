@@ -54,3 +54,38 @@ def test_unaligned_bf16_products():
     # fp32 sums of exact products: 2000 terms, relative error below sqrt(2000) 2^-24 = 3e-6
     assert rel_l2(dX.double().cpu().numpy(), dY @ W) <= 1e-5
     assert rel_l2(dW.double().cpu().numpy(), 1.0 + mmdit.wgrad(dY, X)) <= 1e-5
+
+
+# bf16 products of 64 x 64 and 128 x 128 direct-to-LDS tiles and 128 x 128 register-staged ones: one row below, at and
+# above a tile edge, one k tile, ragged k in the weight gradient (rows), K = 96 (not a multiple of 64)
+@pytest.mark.parametrize("rows,n_out,n_in", [(8, 64, 64), (63, 96, 72), (65, 64, 136), (129, 768, 200), (127, 2048, 1024),
+                                             (1089, 1536, 768), (2500, 1544, 1536)])
+def test_bf16_product_tiles(rows, n_out, n_in):
+    dY = rounded(synth.normal((rows, n_out), 5), torch.bfloat16)
+    X = rounded(synth.normal((rows, n_in), 6), torch.bfloat16)
+    W = rounded(synth.normal((n_out, n_in), 7, scale=0.02), torch.bfloat16)
+    ctx = pk.Context(pk.config("tiny"))
+    dX = torch.empty(rows, n_in, dtype=torch.float32, device="cuda")
+    dYd, Xd, Wd = (to_dev(x, torch.bfloat16) for x in (dY, X, W))
+    ctx.linear_grad(pk.DGRAD, dYd, Wd, dX)
+    # the row past the last one of X and dY must not reach the sums: rows of a larger allocation, the rest NaN
+    big = torch.full((rows + 64, n_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+    big[:rows] = Xd
+    dW = torch.ones(n_out, n_in, dtype=torch.float32, device="cuda")
+    ctx.linear_grad(pk.WGRAD, dYd, big[:rows], dW, beta=1.0)
+    dWb = torch.ones(n_out, n_in, dtype=torch.bfloat16, device="cuda")
+    ctx.linear_grad(pk.WGRAD, dYd, big[:rows], dWb, beta=1.0)
+    want = 1.0 + mmdit.wgrad(dY, X)
+    # fp32 sums of exact products (K <= 2500: below 1e-5); one bf16 rounding is 2^-9 at most
+    assert rel_l2(dX.double().cpu().numpy(), dY @ W) <= 1e-5
+    assert rel_l2(dW.double().cpu().numpy(), want) <= 1e-5
+    assert rel_l2(dWb.double().cpu().numpy(), want) <= 8e-3
+
+
+@pytest.mark.parametrize("c,B", [
+    (block(6, 128, 77, 10, 14, act=pk.BF16), 1),   # 64 x 64 tiles
+    (block(6, 128, 77, 34, 38, act=pk.BF16, block_only=0, n_single=1), 2),   # 128 x 128 and 64 x 64
+    (block(3, 32, 9, 6, 6, act=pk.BF16), 1),  # K = 96 and 288
+], ids=["tiles64", "tiles128", "k96"])
+def test_bf16_products_of_a_pass(c, B):
+    check_pass(c, B, 3, 2e-2)
