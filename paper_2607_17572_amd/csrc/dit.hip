@@ -313,9 +313,8 @@ static size_t plan_ws(const Model& m, int B, void* base, Ws& W) {
   W.tmp = a.f32((size_t)B * m.D);
   // partials of every small-linear backward with an input gradient: the
   // modulations (D -> 6D or 3D or 2D) and the second time-MLP layer (D -> D)
-  const size_t slp = std::max({small_linear_bwd_part_floats(B, m.D, 6 * m.D), small_linear_bwd_part_floats(B, m.D, 3 * m.D),
-                               small_linear_bwd_part_floats(B, m.D, 2 * m.D), small_linear_bwd_part_floats(B, m.D, m.D),
-                               small_linear_bwd_part_floats(B, m.tf, m.D)});
+  const size_t slp = std::max({small_linear_bwd_part_floats(B, m.D, 6 * m.D, 2), small_linear_bwd_part_floats(B, m.D, 3 * m.D, 1),
+                               small_linear_bwd_part_floats(B, m.D, 2 * m.D, 1), small_linear_bwd_part_floats(B, m.D, m.D, 1)});
   W.slpart = a.f32(slp);
   W.gact = a.take(rows * m.D * es);
   if (!m.c.block_only) {
@@ -442,8 +441,8 @@ static int dbl_fwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
   const size_t es = dsize(m.act);
   auto row = [&](void* p, int r, int ld) { return (void*)((char*)p + (size_t)r * ld * es); };
   const auto& st = m.dbl[i];
-  for (int s = 0; s < 2; ++s)
-    TRY(small_linear_fwd(mvec, 0, B, D, cx.P(st[s].mod.w), cx.P(st[s].mod.b), m.act, A.mod[s], 6 * D, cx.s));
+  const SmallLin mod[2] = {{cx.P(st[0].mod.w), cx.P(st[0].mod.b), A.mod[0]}, {cx.P(st[1].mod.w), cx.P(st[1].mod.b), A.mod[1]}};
+  TRY(small_linear_fwd(mvec, B, D, mod, 2, m.act, 6 * D, cx.s));
   TRY(ln_mod_fwd(A.x_in, m.act, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 0, D, A.a1, A.m1, A.r1, cx.s));
   // the two streams' products of each layer: one grouped launch
   auto fwd2 = [&](void* X, int ldx, const Lin& L0, const Lin& L1, int nout, void* Y, int ldy, int mode = EPI_STORE,
@@ -476,7 +475,8 @@ static int sgl_fwd(const Ctx& cx, int i, const SglAct& A, const float* mvec, int
   const int R = rm.rows();
   const size_t es = dsize(m.act);
   const SBlock& sb = m.sgl[i];
-  TRY(small_linear_fwd(mvec, 0, B, D, cx.P(sb.mod.w), cx.P(sb.mod.b), m.act, A.mod, 3 * D, cx.s));
+  const SmallLin mod{cx.P(sb.mod.w), cx.P(sb.mod.b), A.mod};
+  TRY(small_linear_fwd(mvec, B, D, &mod, 1, m.act, 3 * D, cx.s));
   TRY(ln_mod_fwd(A.x_in, m.act, D, rm, 0, R, A.mod, A.mod, 3 * D, 0, D, A.a, A.m, A.r, cx.s));
   TRY(lin_fwd(cx, A.a, D, R, sb.in, 0, 3 * D, A.proj, LD));
   TRY(lin_fwd(cx, A.a, D, R, sb.in, 3 * D, F, (char*)A.cat + D * es, LC, EPI_GELU_FWD, (char*)A.proj + 3 * D * es,
@@ -519,10 +519,9 @@ static int forward(jagg_ctx* ctx, const void* theta, const void* z, const float*
   TVals tv;
   for (int b = 0; b < B; ++b) tv.t[b] = t[b];
   TRY(time_embed(tv, B, m.tf, gl.temb, cx.s));
-  TRY(small_linear_fwd(gl.temb, 0, B, m.tf, cx.P(m.t_in.w), cx.P(m.t_in.b), m.act, gl.h1, D, cx.s));
-  TRY(silu_fwd(gl.h1, gl.sh1, (size_t)B * D, cx.s));
-  TRY(small_linear_fwd(gl.sh1, 0, B, D, cx.P(m.t_out.w), cx.P(m.t_out.b), m.act, gl.vec, D, cx.s));
-  TRY(silu_fwd(gl.vec, gl.mvec, (size_t)B * D, cx.s));
+  const SmallLin t_in{cx.P(m.t_in.w), cx.P(m.t_in.b), gl.h1, gl.sh1}, t_out{cx.P(m.t_out.w), cx.P(m.t_out.b), gl.vec, gl.mvec};
+  TRY(small_linear_fwd(gl.temb, B, m.tf, &t_in, 1, m.act, D, cx.s));
+  TRY(small_linear_fwd(gl.sh1, B, D, &t_out, 1, m.act, D, cx.s));
   if (m.c.block_only) {
     if (hipMemcpyAsync(gl.x0, z, (size_t)R * D * es, hipMemcpyDeviceToDevice, cx.s) != hipSuccess) {
       set_error("forward: copy of the input token rows failed");
@@ -563,7 +562,8 @@ static int forward(jagg_ctx* ctx, const void* theta, const void* z, const float*
     }
     return 0;
   }
-  TRY(small_linear_fwd(gl.mvec, 0, B, D, cx.P(m.fmod.w), cx.P(m.fmod.b), m.act, gl.fmod, 2 * D, cx.s));
+  const SmallLin fmod{cx.P(m.fmod.w), cx.P(m.fmod.b), gl.fmod};
+  TRY(small_linear_fwd(gl.mvec, B, D, &fmod, 1, m.act, 2 * D, cx.s));
   TRY(ln_mod_fwd(x, m.act, D, rm, rt, R - rt, gl.fmod, gl.fmod, 2 * D, 0, D, gl.fa, gl.fm, gl.fr, cx.s));
   TRY(lin_fwd(cx, (char*)gl.fa + (size_t)rt * D * es, D, B * m.ni, m.fin, 0, m.pd, W.fout, m.pd));
   TRY(unpatchify(W.fout, m.act, B, m.C, m.c.lat_h, m.c.lat_w, m.p, v_out, cx.s));
@@ -728,10 +728,10 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
   // the modulation sums of the two gates and the second LayerNorm
   TRY(cx.wait_mark());
   // adaLN modulation: mod = SiLU(vec) W_mod^T + b, per stream; d SiLU(vec) in the order text, image
-  for (int s = 0; s < 2; ++s) {
-    TRY(small_linear_bwd(W.dmod[s], mvec, 0, B, D, cx.P(st[s].mod.w), m.act, 6 * D, G(dth, m, st[s].mod.w),
-                         G(dth, m, st[s].mod.b), m.grad, beta, W.dmvec, W.slpart, S, true));
-  }
+  SmallLinGrad mg[2];
+  for (int s = 0; s < 2; ++s)
+    mg[s] = {W.dmod[s], nullptr, cx.P(st[s].mod.w), G(dth, m, st[s].mod.w), G(dth, m, st[s].mod.b)};
+  TRY(small_linear_bwd(mvec, B, D, mg, 2, m.act, 6 * D, m.grad, beta, W.dmvec, W.slpart, S, true));
   TRY(cx.join());  // the next block reuses W.dY and W.dbig
   (void)rowf;
   return 0;
@@ -778,8 +778,8 @@ static int sgl_bwd(const Ctx& cx, int i, const SglAct& A, const float* mvec, int
                          per_sample_job(W.p2, D, rm, 0, R, W.dmod[0], 3 * D, 0, LN_ROWS)};
     TRY(reduce_jobs(j, 2, cx.s));
   }
-  TRY(small_linear_bwd(W.dmod[0], mvec, 0, B, D, cx.P(L.mod.w), m.act, 3 * D, G(dth, m, L.mod.w), G(dth, m, L.mod.b),
-                       m.grad, beta, W.dmvec, W.slpart, cx.s, true));
+  const SmallLinGrad mg{W.dmod[0], nullptr, cx.P(L.mod.w), G(dth, m, L.mod.w), G(dth, m, L.mod.b)};
+  TRY(small_linear_bwd(mvec, B, D, &mg, 1, m.act, 3 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, true));
   return 0;
 }
 
@@ -855,8 +855,8 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
                    W.p2, cx.s));
     TRY(reduce_per_sample(W.p1, D, rm, rt, R - rt, W.dmod[0], 2 * D, D, cx.s, LN_ROWS));
     TRY(reduce_per_sample(W.p2, D, rm, rt, R - rt, W.dmod[0], 2 * D, 0, cx.s, LN_ROWS));
-    TRY(small_linear_bwd(W.dmod[0], gl.mvec, 0, B, D, cx.P(m.fmod.w), act, 2 * D, G(dth, m, m.fmod.w),
-                         G(dth, m, m.fmod.b), m.grad, beta, W.dmvec, W.slpart, cx.s, true));
+    const SmallLinGrad mg{W.dmod[0], nullptr, cx.P(m.fmod.w), G(dth, m, m.fmod.w), G(dth, m, m.fmod.b)};
+    TRY(small_linear_bwd(gl.mvec, B, D, &mg, 1, act, 2 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, true));
   }
   for (int i = m.c.n_single - 1; i >= 0; --i) {
     SglAct A = S.s[i];
@@ -898,12 +898,10 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
   }
   (void)nchunk;
   // time MLP: vec = SiLU(temb W1^T + b1) W2^T + b2; modulations read SiLU(vec)
-  TRY(mul_silu_grad(W.dmvec, gl.vec, (size_t)B * D, cx.s));
-  TRY(small_linear_bwd(W.dmvec, gl.sh1, 0, B, D, cx.P(m.t_out.w), act, D, G(dth, m, m.t_out.w), G(dth, m, m.t_out.b),
-                       m.grad, beta, W.dsh1, W.slpart, cx.s));
-  TRY(mul_silu_grad(W.dsh1, gl.h1, (size_t)B * D, cx.s));
-  TRY(small_linear_bwd(W.dsh1, gl.temb, 0, B, m.tf, cx.P(m.t_in.w), act, D, G(dth, m, m.t_in.w), G(dth, m, m.t_in.b),
-                       m.grad, beta, nullptr, W.slpart, cx.s));
+  const SmallLinGrad go{W.dmvec, gl.vec, cx.P(m.t_out.w), G(dth, m, m.t_out.w), G(dth, m, m.t_out.b)};
+  TRY(small_linear_bwd(gl.sh1, B, D, &go, 1, act, D, m.grad, beta, W.dsh1, W.slpart, cx.s));
+  const SmallLinGrad gi{W.dsh1, gl.h1, cx.P(m.t_in.w), G(dth, m, m.t_in.w), G(dth, m, m.t_in.b)};
+  TRY(small_linear_bwd(gl.temb, B, m.tf, &gi, 1, act, D, m.grad, beta, nullptr, W.slpart, cx.s));
   return 0;
 }
 

@@ -30,25 +30,36 @@ constexpr int RED_ROWS = 32;  // rows per reduction chunk
 constexpr int LN_ROWS = 8;
 
 // ---- small-M linear layers (time MLP, adaLN modulation): M = batch <= 64 ----
-// out[b][j] = sum_d act(in[b][d]) W[j][d] + bias[j];  act: 0 identity, 1 SiLU.
-int small_linear_fwd(const float* in, int act, int B, int Din, const void* W, const void* bias, int w_dt,
-                     float* out, int Dout, hipStream_t s);
-// dW[j][d] (+)= sum_b dout[b][j] act(in[b][d]) ; db[j] (+)= sum_b dout[b][j];
-// din[b][d] (+)= sum_j dout[b][j] W[j][d]  (fp32, overwritten, or added to
-// when din_acc; nullptr to skip).
+// One or two problems on the same input (a double block's text and image
+// modulation) per launch.
+// out[b][j] = sum_d in[b][d] W[j][d] + bias[j]; silu_out (optional) = SiLU(out).
+struct SmallLin {
+  const void* W = nullptr;
+  const void* bias = nullptr;
+  float* out = nullptr;
+  float* silu_out = nullptr;
+};
+int small_linear_fwd(const float* in, int B, int Din, const SmallLin* p, int np, int w_dt, int Dout, hipStream_t s);
+// With g[b][j] = dout[b][j], times SiLU'(pre[b][j]) when pre is given (the
+// layer's output went through SiLU):
+// dW[j][d] (+)= sum_b g[b][j] in[b][d]; db[j] (+)= sum_b g[b][j];
+// din[b][d] (+)= sum over problems and j of g[b][j] W[j][d]  (fp32,
+// overwritten, or added to when din_acc; nullptr to skip).
 // `part` is workspace of small_linear_bwd_part_floats() floats.
-size_t small_linear_bwd_part_floats(int B, int Din, int Dout);
-int small_linear_bwd(const float* dout, const float* in, int act, int B, int Din, const void* W, int w_dt,
-                     int Dout, void* dW, void* db, int g_dt, float beta, float* din, float* part,
-                     hipStream_t s, bool din_acc = false);
+struct SmallLinGrad {
+  const float* dout = nullptr;
+  const float* pre = nullptr;
+  const void* W = nullptr;
+  void* dW = nullptr;
+  void* db = nullptr;
+};
+size_t small_linear_bwd_part_floats(int B, int Din, int Dout, int np);
+int small_linear_bwd(const float* in, int B, int Din, const SmallLinGrad* p, int np, int w_dt, int Dout, int g_dt,
+                     float beta, float* din, float* part, hipStream_t s, bool din_acc = false);
 
 // ---- time embedding: temb[b][k] = cos(1000 t_b w_k), temb[b][F/2+k] = sin(...) ----
 struct TVals { float t[64]; };
 int time_embed(const TVals& tv, int B, int F, float* temb, hipStream_t s);
-
-// elementwise y = f(x) on fp32 arrays: op 0 silu, 1 silu_grad-multiply (y = y * silu'(x))
-int silu_fwd(const float* x, float* y, size_t n, hipStream_t s);
-int mul_silu_grad(float* y, const float* x, size_t n, hipStream_t s);
 
 // ---- LayerNorm (no affine) + adaLN modulate ----
 // a = LN(x) * (1 + scale[b]) + shift[b]; rows [row0, row0 + nrows) of the map.

@@ -96,14 +96,71 @@ __device__ inline void st8f(float* p, const float* f) {
 static inline bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // ================================================================ small linear
+// Narrow loads and stores of N consecutive elements (16-byte ones for N = 8).
+template <int N>
+__device__ inline void ldn(const uint16_t* p, float* f) {
+  if constexpr (N == 8) {
+    ld8f(p, f);
+  } else {
+    typedef uint32_t uv __attribute__((ext_vector_type(N / 2)));
+    const uv u = *(const uv*)p;
+#pragma unroll
+    for (int e = 0; e < N / 2; ++e) { f[2 * e] = bf2f(u[e] & 0xffffu); f[2 * e + 1] = bf2f(u[e] >> 16); }
+  }
+}
+template <int N>
+__device__ inline void ldn(const float* p, float* f) {
+  typedef float fv __attribute__((ext_vector_type(N < 4 ? N : 4)));
+  constexpr int C = N < 4 ? N : 4;
+#pragma unroll
+  for (int i = 0; i < N / C; ++i) {
+    const fv v = *(const fv*)(p + C * i);
+#pragma unroll
+    for (int e = 0; e < C; ++e) f[C * i + e] = v[e];
+  }
+}
+template <int N>
+__device__ inline void stn(uint16_t* p, const float* f) {
+  if constexpr (N == 8) {
+    st8f(p, f);
+  } else {
+    typedef uint32_t uv __attribute__((ext_vector_type(N / 2)));
+    uv u;
+#pragma unroll
+    for (int e = 0; e < N / 2; ++e) u[e] = f2bf(f[2 * e]) | ((uint32_t)f2bf(f[2 * e + 1]) << 16);
+    *(uv*)p = u;
+  }
+}
+template <int N>
+__device__ inline void stn(float* p, const float* f) {
+  typedef float fv __attribute__((ext_vector_type(N < 4 ? N : 4)));
+  constexpr int C = N < 4 ? N : 4;
+#pragma unroll
+  for (int i = 0; i < N / C; ++i) {
+    fv v;
+#pragma unroll
+    for (int e = 0; e < C; ++e) v[e] = f[C * i + e];
+    *(fv*)(p + C * i) = v;
+  }
+}
+
+struct SmallLin2 { SmallLin p[2]; };
+struct SmallLinGrad2 { SmallLinGrad p[2]; };
+
+__device__ inline void small_linear_store(const SmallLin& p, size_t i, float v) {
+  p.out[i] = v;
+  if (p.silu_out) p.silu_out[i] = silu(v);
+}
+
+// One output row per wave, any width and alignment.
 template <typename TW>
-__global__ __launch_bounds__(256) void small_linear_fwd_k(const float* __restrict__ in, int B, int Din,
-                                                          const TW* __restrict__ W, const TW* __restrict__ bias,
-                                                          float* __restrict__ out, int Dout) {
+__global__ __launch_bounds__(256) void small_linear_fwd_k(const float* __restrict__ in, int B, int Din, SmallLin2 sp,
+                                                          int Dout) {
+  const SmallLin& p = sp.p[blockIdx.y];
   const int lane = threadIdx.x & 63;
   const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= Dout) return;
-  const TW* w = W + (size_t)j * Din;
+  const TW* w = (const TW*)p.W + (size_t)j * Din;
   for (int b0 = 0; b0 < B; b0 += 8) {
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int d = lane; d < Din; d += 64) {
@@ -115,138 +172,132 @@ __global__ __launch_bounds__(256) void small_linear_fwd_k(const float* __restric
 #pragma unroll
     for (int bb = 0; bb < 8; ++bb) {
       const float s = wave_sum(acc[bb]);
-      if (lane == 0 && b0 + bb < B) out[(size_t)(b0 + bb) * Dout + j] = s + (bias ? ldf(bias, j) : 0.f);
+      if (lane == 0 && b0 + bb < B) small_linear_store(p, (size_t)(b0 + bb) * Dout + j, s + ldf((const TW*)p.bias, j));
     }
   }
 }
 
-// Wide rows (Din a multiple of 512): two output rows per wave, each lane
-// reads 8 consecutive weights per 16-byte load (a wave streams 1 KB of W per
-// instruction), the batch's inputs are read as 8-float vectors from cache.
-template <typename TW>
-__global__ __launch_bounds__(256) void small_linear_fwd_vec_k(const float* __restrict__ in, int B, int Din,
-                                                              const TW* __restrict__ W, const TW* __restrict__ bias,
-                                                              float* __restrict__ out, int Dout) {
+// Sums v[0..N) over the wave's 64 lanes (N a power of two up to 32), halving
+// the values a lane carries in each exchange: N - 1 + log2(64 / N) exchanges
+// instead of 6 N.  Lane L returns the sum of value reduce_index<N>(L); the
+// lanes of a value hold the same sum.
+template <int N, int M = 32>
+__device__ __forceinline__ float wave_reduce(float (&v)[N]) {
   const int lane = threadIdx.x & 63;
-  const int j0 = blockIdx.x * 8 + 2 * (threadIdx.x >> 6);
+  if constexpr (N == 1) {
+    float s = v[0];
+#pragma unroll
+    for (int o = M; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    return s;
+  } else {
+    const bool up = lane & M;
+    float r[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const float keep = up ? v[i + N / 2] : v[i], give = up ? v[i] : v[i + N / 2];
+      r[i] = keep + __shfl_xor(give, M, 64);
+    }
+    return wave_reduce<N / 2, M / 2>(r);
+  }
+}
+template <int N>
+__device__ __forceinline__ int reduce_index(int lane) { return lane / (64 / N); }
+
+// SLF_R output rows per wave: bound by streaming W once, so each lane has
+// SLF_R 16-byte weight loads in flight, and the batch's inputs (8-float
+// vectors from cache, BM samples per pass) serve SLF_R rows per read.
+// Measured (both streams' modulations of a double block; two rows per wave,
+// four samples per pass, a launch each and 6 exchanges per sum before): 2 x
+// 18432 x 3072 at batch 2 71.8 -> 63.3 us, 2 x 9216 x 1536 at batch 6 32.1 ->
+// 21.9 us, 2 x 4608 x 768 at batch 8 (then one row per wave) 51.8 -> 12.5 us.
+constexpr int SLF_R = 4;
+template <typename TW, int BM>
+__global__ __launch_bounds__(256) void small_linear_fwd_vec_k(const float* __restrict__ in, int B, int Din,
+                                                              SmallLin2 sp, int Dout) {
+  const SmallLin& p = sp.p[blockIdx.y];
+  const int lane = threadIdx.x & 63;
+  const int j0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * SLF_R;
   if (j0 >= Dout) return;
-  const bool two = j0 + 1 < Dout;
-  const TW* w0 = W + (size_t)j0 * Din;
-  const TW* w1 = W + (size_t)(two ? j0 + 1 : j0) * Din;
-  for (int b0 = 0; b0 < B; b0 += 4) {
-    float acc[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  const TW* w[SLF_R];
+#pragma unroll
+  for (int r = 0; r < SLF_R; ++r) w[r] = (const TW*)p.W + (size_t)min(j0 + r, Dout - 1) * Din;
+  for (int b0 = 0; b0 < B; b0 += BM) {
+    float acc[SLF_R * BM];
+#pragma unroll
+    for (int i = 0; i < SLF_R * BM; ++i) acc[i] = 0.f;
+#pragma unroll 2
     for (int d = 8 * lane; d < Din; d += 512) {
-      float a[8], c[8];
-      ld8f(w0 + d, a);
-      ld8f(w1 + d, c);
+      Raw8<TW> a[SLF_R];
 #pragma unroll
-      for (int bb = 0; bb < 4; ++bb) {
-        if (b0 + bb >= B) break;
+      for (int r = 0; r < SLF_R; ++r) a[r].load(w[r] + d);
+#pragma unroll
+      for (int b = 0; b < BM; ++b) {
+        if (b0 + b >= B) continue;
         float x[8];
-        ld8f(in + (size_t)(b0 + bb) * Din + d, x);
+        ld8f(in + (size_t)(b0 + b) * Din + d, x);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          acc[0][bb] = fmaf(a[e], x[e], acc[0][bb]);
-          acc[1][bb] = fmaf(c[e], x[e], acc[1][bb]);
-        }
+        for (int r = 0; r < SLF_R; ++r)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[r * BM + b] = fmaf(a[r][e], x[e], acc[r * BM + b]);
       }
     }
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb) {
-      const float s0 = wave_sum(acc[0][bb]), s1 = wave_sum(acc[1][bb]);
-      if (lane == 0 && b0 + bb < B) {
-        out[(size_t)(b0 + bb) * Dout + j0] = s0 + (bias ? ldf(bias, j0) : 0.f);
-        if (two) out[(size_t)(b0 + bb) * Dout + j0 + 1] = s1 + (bias ? ldf(bias, j0 + 1) : 0.f);
-      }
-    }
+    const float s = wave_reduce<SLF_R * BM>(acc);
+    const int i = reduce_index<SLF_R * BM>(lane), j = j0 + i / BM, b = b0 + i % BM;
+    if (lane % (64 / (SLF_R * BM)) == 0 && j < Dout && b < B)
+      small_linear_store(p, (size_t)b * Dout + j, s + ldf((const TW*)p.bias, j));
   }
 }
 
-int small_linear_fwd(const float* in, int act, int B, int Din, const void* W, const void* bias, int w_dt,
-                     float* out, int Dout, hipStream_t s) {
-  if (act != 0 || B <= 0 || B > 64) { set_error("small_linear_fwd: bad batch/act"); return 1; }
-  if (Din % 512 == 0 && al16(in) && al16(W)) {
-    dim3 grid((Dout + 7) / 8);
-    if (w_dt == BF16)
-      hipLaunchKernelGGL(small_linear_fwd_vec_k<uint16_t>, grid, dim3(256), 0, s, in, B, Din, (const uint16_t*)W,
-                         (const uint16_t*)bias, out, Dout);
-    else
-      hipLaunchKernelGGL(small_linear_fwd_vec_k<float>, grid, dim3(256), 0, s, in, B, Din, (const float*)W,
-                         (const float*)bias, out, Dout);
-    LAUNCH_OK("small_linear_fwd_vec");
-    return 0;
+template <typename TW>
+static void small_linear_fwd_t(const float* in, int B, int Din, const SmallLin2& sp, int np, int Dout, bool vec,
+                               hipStream_t s) {
+  if (!vec) {
+    hipLaunchKernelGGL(small_linear_fwd_k<TW>, dim3((Dout + 3) / 4, np), dim3(256), 0, s, in, B, Din, sp, Dout);
+    return;
   }
-  dim3 grid((Dout + 3) / 4);
-  if (w_dt == BF16)
-    hipLaunchKernelGGL(small_linear_fwd_k<uint16_t>, grid, dim3(256), 0, s, in, B, Din, (const uint16_t*)W,
-                       (const uint16_t*)bias, out, Dout);
-  else
-    hipLaunchKernelGGL(small_linear_fwd_k<float>, grid, dim3(256), 0, s, in, B, Din, (const float*)W,
-                       (const float*)bias, out, Dout);
+  const dim3 grid((Dout + 4 * SLF_R - 1) / (4 * SLF_R), np);
+  if (B <= 2) hipLaunchKernelGGL((small_linear_fwd_vec_k<TW, 2>), grid, dim3(256), 0, s, in, B, Din, sp, Dout);
+  else if (B <= 4) hipLaunchKernelGGL((small_linear_fwd_vec_k<TW, 4>), grid, dim3(256), 0, s, in, B, Din, sp, Dout);
+  else hipLaunchKernelGGL((small_linear_fwd_vec_k<TW, 8>), grid, dim3(256), 0, s, in, B, Din, sp, Dout);
+}
+
+int small_linear_fwd(const float* in, int B, int Din, const SmallLin* p, int np, int w_dt, int Dout, hipStream_t s) {
+  if (np < 1 || np > 2 || B <= 0 || B > 64) { set_error("small_linear_fwd: bad batch"); return 1; }
+  SmallLin2 sp{};
+  bool vec = Din % 8 == 0 && al16(in);
+  for (int i = 0; i < np; ++i) {
+    sp.p[i] = p[i];
+    vec = vec && al16(p[i].W);
+  }
+  if (w_dt == BF16) small_linear_fwd_t<uint16_t>(in, B, Din, sp, np, Dout, vec, s);
+  else small_linear_fwd_t<float>(in, B, Din, sp, np, Dout, vec, s);
   LAUNCH_OK("small_linear_fwd");
   return 0;
 }
 
-constexpr int SL_JT = 64;   // output rows per tile
-constexpr int SL_DT = 256;  // input columns per tile (one per thread)
+constexpr int SL_JT = 64;   // output rows per block, at most
 constexpr int SL_MAXB = 32;
 
-// Output rows per block of the vector kernel: enough blocks (~1024) to keep
-// every CU streaming W and dW, at most SL_JT; the input-gradient partials
-// grow with the block-row count.
-static int sl_rows(int Din, int Dout) {
-  const long cb = (Din + 1023) / 1024;
-  const long r = cb * Dout / 1024 / 8 * 8;
+// Input columns per thread: the batch's inputs and input-gradient sums of
+// those columns stay in registers (64 of each at most).
+static int sl_cpt(int B) { return B <= 4 ? 8 : B <= 8 ? 4 : 2; }
+
+// Output rows per block: enough blocks (~1024) to keep every CU streaming W
+// and dW, at most SL_JT; the input-gradient partials grow with the number of
+// row blocks.
+static int sl_rows(int cpt, int Din, int Dout, int np) {
+  const long cb = (Din + 128 * cpt - 1) / (128 * cpt);
+  const long r = np * cb * Dout / 1024 / 8 * 8;
   return (int)std::max<long>(8, std::min<long>(SL_JT, r));
 }
-
-size_t small_linear_bwd_part_floats(int B, int Din, int Dout) {
-  const int jt = std::min(SL_JT, sl_rows(Din, Dout));
-  return (size_t)((Dout + jt - 1) / jt) * B * Din;
+static int sl_parts(int cpt, int Din, int Dout, int np) {
+  const int jt = sl_rows(cpt, Din, Dout, np);
+  return (Dout + jt - 1) / jt;
 }
 
-template <typename TW, typename TG>
-__global__ __launch_bounds__(256) void small_linear_bwd_k(const float* __restrict__ dout, const float* __restrict__ in,
-                                                          int B, int Din, const TW* __restrict__ W, int Dout,
-                                                          TG* __restrict__ dW, TG* __restrict__ db, float beta,
-                                                          float* __restrict__ part) {
-  __shared__ float sd[SL_MAXB][SL_JT];
-  const int jt = blockIdx.y, j0 = jt * SL_JT;
-  const int d = blockIdx.x * SL_DT + threadIdx.x;
-  for (int i = threadIdx.x; i < B * SL_JT; i += 256) {
-    const int b = i / SL_JT, jj = i % SL_JT;
-    sd[b][jj] = (j0 + jj < Dout) ? dout[(size_t)b * Dout + j0 + jj] : 0.f;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0 && db) {
-    for (int jj = threadIdx.x; jj < SL_JT; jj += 256) {
-      if (j0 + jj >= Dout) continue;
-      float s = 0.f;
-      for (int b = 0; b < B; ++b) s += sd[b][jj];
-      if (beta != 0.f) s += beta * ldf(db, j0 + jj);
-      stf(db, j0 + jj, s);
-    }
-  }
-  if (d >= Din) return;
-  float x[SL_MAXB], acc[SL_MAXB];
-  for (int b = 0; b < B; ++b) { x[b] = in[(size_t)b * Din + d]; acc[b] = 0.f; }
-  const int jn = min(SL_JT, Dout - j0);
-  // rows are independent apart from the input-gradient sums: unrolled so that
-  // the loads of several rows are in flight together
-#pragma unroll 8
-  for (int jj = 0; jj < jn; ++jj) {
-    const size_t idx = (size_t)(j0 + jj) * Din + d;
-    const float w = ldf(W, idx);
-    float g = 0.f;
-    for (int b = 0; b < B; ++b) {
-      g = fmaf(sd[b][jj], x[b], g);
-      acc[b] = fmaf(sd[b][jj], w, acc[b]);
-    }
-    if (beta != 0.f) g += beta * ldf(dW, idx);
-    stf(dW, idx, g);
-  }
-  if (part)
-    for (int b = 0; b < B; ++b) part[((size_t)jt * B + b) * Din + d] = acc[b];
+size_t small_linear_bwd_part_floats(int B, int Din, int Dout, int np) {
+  // rows that are not aligned for the vector kernel take one column per thread
+  return (size_t)np * std::max(sl_parts(sl_cpt(B), Din, Dout, np), sl_parts(1, Din, Dout, np)) * B * Din;
 }
 
 // out[i] (+)= sum over p of part[p * n + i], parts added in a fixed order: 64
@@ -271,19 +322,32 @@ __global__ __launch_bounds__(256) void sum_parts_k(const float* __restrict__ par
   }
 }
 
-// Small batches: 8 consecutive input columns per thread (16-byte loads and
-// stores of W and dW), all samples' rows kept in registers.
-template <typename TW, typename TG, int BM>
-__global__ __launch_bounds__(128) void small_linear_bwd_vec_k(const float* __restrict__ dout,
-                                                              const float* __restrict__ in, int B, int Din,
-                                                              const TW* __restrict__ W, int Dout, TG* __restrict__ dW,
-                                                              TG* __restrict__ db, float beta,
-                                                              float* __restrict__ part, int JT) {
+// CPT consecutive input columns per thread (vector loads and stores of W and
+// dW), BM samples' inputs and input-gradient sums in registers; the z
+// dimension is the problem.  Bound by reading W and writing dW (and reading it
+// when beta is set) once; a version for any batch with one column per thread
+// and its samples in scratch memory took 242 us for the four layers of a block
+// model of hidden 1536 at batch 6 (two of 9216 x 1536, the time MLP's 1536 x
+// 1536 and 1536 x 256) where this takes 50 (the last one 52 -> 5).
+template <typename TW, typename TG, int BM, int CPT>
+__global__ __launch_bounds__(128) void small_linear_bwd_k(const float* __restrict__ in, int B, int Din,
+                                                          SmallLinGrad2 sp, int Dout, float beta,
+                                                          float* __restrict__ part, int JT) {
   __shared__ float sd[BM][SL_JT];
+  const SmallLinGrad& p = sp.p[blockIdx.z];
+  const TW* __restrict__ W = (const TW*)p.W;
+  TG* __restrict__ dW = (TG*)p.dW;
+  TG* __restrict__ db = (TG*)p.db;
   const int jt = blockIdx.y, j0 = jt * JT;
   for (int i = threadIdx.x; i < BM * JT; i += 128) {
     const int b = i / JT, jj = i % JT;
-    sd[b][jj] = (b < B && j0 + jj < Dout) ? dout[(size_t)b * Dout + j0 + jj] : 0.f;
+    float v = 0.f;
+    if (b < B && j0 + jj < Dout) {
+      const size_t o = (size_t)b * Dout + j0 + jj;
+      v = p.dout[o];
+      if (p.pre) v *= silu_grad(p.pre[o]);
+    }
+    sd[b][jj] = v;
   }
   __syncthreads();
   if (blockIdx.x == 0 && db) {
@@ -295,16 +359,16 @@ __global__ __launch_bounds__(128) void small_linear_bwd_vec_k(const float* __res
       stf(db, j0 + jj, sacc);
     }
   }
-  const int d = (blockIdx.x * 128 + threadIdx.x) * 8;
+  const int d = (blockIdx.x * 128 + threadIdx.x) * CPT;
   if (d >= Din) return;
-  float x[BM][8], acc[BM][8];
+  float x[BM][CPT], acc[BM][CPT];
 #pragma unroll
   for (int b = 0; b < BM; ++b) {
-    if (b < B) ld8f(in + (size_t)b * Din + d, x[b]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if (b >= B) x[b][e] = 0.f;
-      acc[b][e] = 0.f;
+    for (int e = 0; e < CPT; ++e) x[b][e] = acc[b][e] = 0.f;
+    if (b < B) {
+      if constexpr (CPT == 1) x[b][0] = in[(size_t)b * Din + d];
+      else ldn<CPT>(in + (size_t)b * Din + d, x[b]);
     }
   }
   const int jn = min(JT, Dout - j0);
@@ -313,72 +377,75 @@ __global__ __launch_bounds__(128) void small_linear_bwd_vec_k(const float* __res
 #pragma unroll 8
   for (int jj = 0; jj < jn; ++jj) {
     const size_t idx = (size_t)(j0 + jj) * Din + d;
-    float w[8], gw[8];
-    ld8f(W + idx, w);
+    float w[CPT], gw[CPT];
+    if constexpr (CPT == 1) w[0] = ldf(W, idx);
+    else ldn<CPT>(W + idx, w);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) gw[e] = 0.f;
+    for (int e = 0; e < CPT; ++e) gw[e] = 0.f;
 #pragma unroll
     for (int b = 0; b < BM; ++b) {
       const float sv = sd[b][jj];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < CPT; ++e) {
         gw[e] = fmaf(sv, x[b][e], gw[e]);
         acc[b][e] = fmaf(sv, w[e], acc[b][e]);
       }
     }
     if (beta != 0.f) {
-      float o[8];
-      ld8f(dW + idx, o);
+      float o[CPT];
+      if constexpr (CPT == 1) o[0] = ldf(dW, idx);
+      else ldn<CPT>(dW + idx, o);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) gw[e] += beta * o[e];
+      for (int e = 0; e < CPT; ++e) gw[e] += beta * o[e];
     }
-    st8f(dW + idx, gw);
+    if constexpr (CPT == 1) stf(dW, idx, gw[0]);
+    else stn<CPT>(dW + idx, gw);
   }
   if (part)
 #pragma unroll
     for (int b = 0; b < BM; ++b)
-      if (b < B) st8f(part + ((size_t)jt * B + b) * Din + d, acc[b]);
+      if (b < B) {
+        float* q = part + (((size_t)blockIdx.z * gridDim.y + jt) * B + b) * Din + d;
+        if constexpr (CPT == 1) *q = acc[b][0];
+        else stn<CPT>(q, acc[b]);
+      }
 }
 
-int small_linear_bwd(const float* dout, const float* in, int act, int B, int Din, const void* W, int w_dt,
-                     int Dout, void* dW, void* db, int g_dt, float beta, float* din, float* part,
-                     hipStream_t s, bool din_acc) {
-  if (act != 0 || B <= 0 || B > SL_MAXB) { set_error("small_linear_bwd: batch must be 1..32"); return 1; }
-  const int njt = (Dout + SL_JT - 1) / SL_JT;
-  if (B <= 4 && Din % 8 == 0 && al16(in) && al16(W) && al16(dW) && (!din || al16(part))) {
-    const int jt = sl_rows(Din, Dout), njv = (Dout + jt - 1) / jt;
-    dim3 grid((Din + 1023) / 1024, njv);
-    float* p = din ? part : nullptr;
-#define SLV(TW, TG) \
-  hipLaunchKernelGGL((small_linear_bwd_vec_k<TW, TG, 4>), grid, dim3(128), 0, s, dout, in, B, Din, (const TW*)W, Dout, \
-                     (TG*)dW, (TG*)db, beta, p, jt)
-    if (w_dt == BF16 && g_dt == BF16) SLV(uint16_t, uint16_t);
-    else if (w_dt == BF16) SLV(uint16_t, float);
-    else if (g_dt == BF16) SLV(float, uint16_t);
-    else SLV(float, float);
-#undef SLV
-    LAUNCH_OK("small_linear_bwd_vec");
-    if (din) {
-      const size_t n = (size_t)B * Din;
-      hipLaunchKernelGGL(sum_parts_k, dim3((n + 63) / 64), dim3(256), 0, s, part, njv, n, din, din_acc);
-      LAUNCH_OK("small_linear_bwd_sum");
-    }
-    return 0;
-  }
-  dim3 grid((Din + SL_DT - 1) / SL_DT, njt);
-  float* p = din ? part : nullptr;
-#define SLB(TW, TG)                                                                                  \
-  hipLaunchKernelGGL((small_linear_bwd_k<TW, TG>), grid, dim3(256), 0, s, dout, in, B, Din, (const TW*)W, \
-                     Dout, (TG*)dW, (TG*)db, beta, p)
-  if (w_dt == BF16 && g_dt == BF16) SLB(uint16_t, uint16_t);
-  else if (w_dt == BF16) SLB(uint16_t, float);
-  else if (g_dt == BF16) SLB(float, uint16_t);
-  else SLB(float, float);
+template <typename TW, typename TG>
+static void small_linear_bwd_t(const float* in, int B, int Din, const SmallLinGrad2& sp, int np, int Dout, float beta,
+                               float* part, int jt, int cpt, hipStream_t s) {
+  const dim3 grid((Din + 128 * cpt - 1) / (128 * cpt), (Dout + jt - 1) / jt, np);
+#define SLB(BM, CPT) \
+  hipLaunchKernelGGL((small_linear_bwd_k<TW, TG, BM, CPT>), grid, dim3(128), 0, s, in, B, Din, sp, Dout, beta, part, jt)
+  if (cpt == 1) SLB(SL_MAXB, 1);
+  else if (B <= 2) SLB(2, 8);
+  else if (B <= 4) SLB(4, 8);
+  else if (B <= 8) SLB(8, 4);
+  else if (B <= 16) SLB(16, 2);
+  else SLB(SL_MAXB, 2);
 #undef SLB
+}
+
+int small_linear_bwd(const float* in, int B, int Din, const SmallLinGrad* p, int np, int w_dt, int Dout, int g_dt,
+                     float beta, float* din, float* part, hipStream_t s, bool din_acc) {
+  if (np < 1 || np > 2 || B <= 0 || B > SL_MAXB) { set_error("small_linear_bwd: batch must be 1..32"); return 1; }
+  SmallLinGrad2 sp{};
+  bool vec = Din % 8 == 0 && al16(in) && (!din || al16(part));
+  for (int i = 0; i < np; ++i) {
+    sp.p[i] = p[i];
+    vec = vec && al16(p[i].W) && al16(p[i].dW);
+  }
+  const int cpt = vec ? sl_cpt(B) : 1, jt = sl_rows(cpt, Din, Dout, np);
+  float* pt = din ? part : nullptr;
+  if (w_dt == BF16 && g_dt == BF16) small_linear_bwd_t<uint16_t, uint16_t>(in, B, Din, sp, np, Dout, beta, pt, jt, cpt, s);
+  else if (w_dt == BF16) small_linear_bwd_t<uint16_t, float>(in, B, Din, sp, np, Dout, beta, pt, jt, cpt, s);
+  else if (g_dt == BF16) small_linear_bwd_t<float, uint16_t>(in, B, Din, sp, np, Dout, beta, pt, jt, cpt, s);
+  else small_linear_bwd_t<float, float>(in, B, Din, sp, np, Dout, beta, pt, jt, cpt, s);
   LAUNCH_OK("small_linear_bwd");
   if (din) {
     const size_t n = (size_t)B * Din;
-    hipLaunchKernelGGL(sum_parts_k, dim3((n + 63) / 64), dim3(256), 0, s, part, njt, n, din, din_acc);
+    hipLaunchKernelGGL(sum_parts_k, dim3((n + 63) / 64), dim3(256), 0, s, part, np * ((Dout + jt - 1) / jt), n, din,
+                       din_acc);
     LAUNCH_OK("small_linear_bwd_sum");
   }
   return 0;
@@ -402,25 +469,6 @@ int time_embed(const TVals& tv, int B, int F, float* temb, hipStream_t s) {
   const int n = B * F / 2;
   hipLaunchKernelGGL(time_embed_k, dim3((n + 255) / 256), dim3(256), 0, s, tv, B, F, temb);
   LAUNCH_OK("time_embed");
-  return 0;
-}
-
-__global__ void silu_k(const float* x, float* y, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] = silu(x[i]);
-}
-__global__ void mul_silu_grad_k(float* y, const float* x, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] *= silu_grad(x[i]);
-}
-int silu_fwd(const float* x, float* y, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(silu_k, dim3((n + 255) / 256), dim3(256), 0, s, x, y, n);
-  LAUNCH_OK("silu");
-  return 0;
-}
-int mul_silu_grad(float* y, const float* x, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(mul_silu_grad_k, dim3((n + 255) / 256), dim3(256), 0, s, y, x, n);
-  LAUNCH_OK("mul_silu_grad");
   return 0;
 }
 

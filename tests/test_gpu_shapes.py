@@ -89,3 +89,12 @@ def test_bf16_product_tiles(rows, n_out, n_in):
 ], ids=["tiles64", "tiles128", "k96"])
 def test_bf16_products_of_a_pass(c, B):
     check_pass(c, B, 3, 2e-2)
+
+
+# time MLP and modulations at each samples-per-thread form of their backward (batch 2, 4, 8, 16, 32 of the pair), rows
+# that are not a multiple of the 8-row tiles, and a frequency width without 16-byte rows
+@pytest.mark.parametrize("B,over", [(1, {}), (2, {}), (3, {}), (6, {}), (13, {}), (2, dict(t_freq_dim=250))],
+                         ids=["pair2", "pair4", "pair6", "pair12", "pair26", "unaligned"])
+def test_modulation_batches(B, over):
+    check_pass(block(3, 16, 2, 4, 4, **over), B, 2, 1e-4)
+    check_pass(block(2, 32, 2, 4, 4, act=pk.BF16, grad_dtype=pk.BF16, **over), B, 2, 2e-2)
