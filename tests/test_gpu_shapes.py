@@ -98,3 +98,16 @@ def test_bf16_products_of_a_pass(c, B):
 def test_modulation_batches(B, over):
     check_pass(block(3, 16, 2, 4, 4, **over), B, 2, 1e-4)
     check_pass(block(2, 32, 2, 4, 4, act=pk.BF16, grad_dtype=pk.BF16, **over), B, 2, 2e-2)
+
+
+# group scores: 16-byte and element loads, a last incomplete step, fewer elements than threads; fp64 sums of exact
+# products differ from numpy's by their order only (n <= 3e5: below n 2^-53)
+@pytest.mark.parametrize("n,off", [(5, 0), (8, 0), (4099, 0), (300007, 0), (4099, 1)])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("W", [2, 5, 8])
+def test_group_score_forms(n, off, dt, W):
+    x = [to_dev(synth.normal((n + off,), 50 + j) + synth.normal((n + off,), 9), dt)[off:] for j in range(W)]
+    ctx = pk.Context(pk.config("tiny"))
+    v = [t.double().cpu().numpy() for t in x]
+    cos = [float(v[i] @ v[j] / np.sqrt((v[i] @ v[i]) * (v[j] @ v[j]))) for i in range(W) for j in range(i + 1, W)]
+    assert abs(ctx.group_score(x) - np.mean(cos)) <= 1e-12
