@@ -1,5 +1,5 @@
 // Flash attention forward and backward on gfx950 MFMA (bf16 in, fp32
-// accumulation), head dim 128.
+// accumulation), head dim 128 and 64 (D in the templates below).
 //
 // Layout trick: every score tile is computed in the orientation whose MFMA
 // accumulator can feed the next MFMA directly as its "B" operand.  With
@@ -269,8 +269,9 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(AttnFwd a) {
 }
 
 // ============================================================== delta
-// delta[b][h][j] = sum_d dO[j][h*128+d] * O[j][h*128+d]; one wave per row,
-// 16 lanes per head, 16-byte loads.
+// delta[b][h][j] = sum_d dO[j][h*D+d] * O[j][h*D+d]; one wave per row, D / 8
+// lanes per head, 16-byte loads.
+template <int D>
 __global__ __launch_bounds__(256) void attn_delta_mfma_k(AttnBwd a) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -282,11 +283,12 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_k(AttnBwd a) {
   else { b = (r - bt) / a.rm.ni; j = a.rm.nt + (r - bt) % a.rm.ni; }
   const uint16_t* O = (const uint16_t*)a.O + (size_t)r * a.ld_o;
   const uint16_t* G = (const uint16_t*)a.dO + (size_t)r * a.ld_do;
-  const int D = a.H * DH;
-  for (int c0 = 0; c0 < D; c0 += 512) {
+  constexpr int LPH = D / 8;
+  const int W = a.H * D;
+  for (int c0 = 0; c0 < W; c0 += 512) {
     const int c = c0 + lane * 8;
     float s = 0.f;
-    if (c < D) {
+    if (c < W) {
       const u32x4 x = *(const u32x4*)(O + c), y = *(const u32x4*)(G + c);
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
@@ -294,12 +296,10 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_k(AttnBwd a) {
         s = fmaf(bf2f(x[w] >> 16), bf2f(y[w] >> 16), s);
       }
     }
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    s += __shfl_xor(s, 4, 64);
-    s += __shfl_xor(s, 8, 64);
-    if ((lane & 15) == 0 && c < D) {
-      const int hd = c / DH;
+#pragma unroll
+    for (int o = 1; o < LPH; o <<= 1) s += __shfl_xor(s, o, 64);
+    if ((lane & (LPH - 1)) == 0 && c < W) {
+      const int hd = c / D;
       const size_t i = ((size_t)b * a.H + hd) * a.N + j;
       a.delta[i] = s;
       // second half of the delta buffer: the log-sum-exp in log2 units, so
@@ -529,19 +529,32 @@ __global__ __launch_bounds__(256) void attn_bwd_q_mfma_k(AttnBwd a) {
 }
 
 // ====================================================== backward, v2
-// Tiles of 64 rows x 128 (one head) are fetched straight into LDS by buffer
+// Tiles of 64 rows x D (one head) are fetched straight into LDS by buffer
 // loads with the LDS bit (no register staging), three k tiles in flight, one
-// barrier per tile.  A tile is stored unpadded, 256 B per row, with the 16-byte
-// chunks of row r XOR-swizzled by asw(r); the table makes both fragment
-// patterns conflict-free whether the LDS serves 8 or 16 lanes per cycle:
+// barrier per tile.  A tile is stored unpadded, 2 D bytes per row, with the
+// 16-byte chunks of row r XOR-swizzled by asw<D>(r); the swizzle makes both
+// fragment patterns conflict-free whether the LDS serves 8 or 16 lanes per
+// cycle:
 //   row fragments (16-byte reads, 8/16 consecutive rows, one chunk) and
 //   transposed fragments (ds_read_b64_tr_b16: 4 consecutive rows x 32 B per
 //   16 lanes), which replace the transposed tile copies: lane i of a 16-lane
 //   group receives element (row e, column i) of the 4 x 16 block the group
 //   fetched, so two such reads give the A operand of a product that contracts
 //   over the tile rows, in the row order the accumulator-fed B operand uses.
+// D = 128 (256-byte rows, 16 chunks): a table over r % 16.  D = 64 (128-byte
+// rows: odd rows start half way through the banks): the 3 bits of r / 2 % 8
+// rotated left, so that row pairs 2i and 2i + 1 differ above the lowest chunk
+// bit, which the two chunks of a transposing read use.
 constexpr unsigned long long ASW = 0xf953e842db71ca60ull;
-__device__ __forceinline__ int asw(int r) { return (int)((ASW >> (4 * (r & 15))) & 15); }
+template <int D>
+__device__ __forceinline__ int asw(int r) {
+  if constexpr (D == 128) {
+    return (int)((ASW >> (4 * (r & 15))) & 15);
+  } else {
+    const int x = (r >> 1) & 7;
+    return ((x << 1) & 7) | (x >> 2);
+  }
+}
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 #define ALDS(p) ((__attribute__((address_space(3))) void*)(p))
@@ -555,76 +568,91 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t arsrc(const void* p, long byte
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)bytes, 0x00020000);
 }
 
-// Per-lane constants of one 64-row tile: direct-load slots and fragment offsets.
-struct ATile {
-  int lrow[4], lchunk[4];  // direct loads: tile row and source chunk of this lane, per load
-  int roff[8];             // row fragment, k16 step kb: byte offset for tile row (lane % 32)
-  int t1[4], t2[4];        // transposed fragment, 32-column block dt: the two reads
-  __device__ inline void init() {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      lrow[t] = 4 * (wave * 4 + t) + lane / 16;
-      lchunk[t] = (lane % 16) ^ asw(lrow[t]);
-    }
-    const int rr = lane & 31, h = lane >> 5;
-#pragma unroll
-    for (int kb = 0; kb < 8; ++kb) roff[kb] = rr * 256 + (((2 * kb + h) ^ asw(rr)) << 4);
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      const int2 o = tr_off(lane, dt);
-      t1[dt] = o.x;
-      t2[dt] = o.y;
-    }
-  }
-  // byte offsets of the two transposing reads of column block dt for this lane
+// Direct load of SZ (16 or 4) bytes per lane into LDS.  (Builtins of the device
+// live in functions: inside a kernel template the host pass would look for them.)
+template <int SZ>
+__device__ __forceinline__ void lds_load(__amdgpu_buffer_rsrc_t R, void* S, int off) {
+  if constexpr (SZ == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(R, ALDS(S), 16, off, 0, 0, 0);
+  else __builtin_amdgcn_raw_ptr_buffer_load_lds(R, ALDS(S), 4, off, 0, 0, 0);
+}
+// Two dwords of each half-wave traded: the upper half's a for the lower half's b.
+__device__ __forceinline__ u32x2 half_swap(unsigned a, unsigned b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return u32x2{r[0], r[1]};
+}
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t R, u32x4 v, int off) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, R, off, 0, 0);
+}
+
+// the transposed fragment of the two reads at byte offsets o1, o2
+__device__ inline bf16x8 tr_pair(const char* S, int o1, int o2) {
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + o1));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + o2));
+  const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+// Geometry of a tile with D columns.
+template <int D>
+struct AGeo {
+  static constexpr int ROWB = D * 2, CH = D / 8;   // bytes and 16-byte chunks per row
+  static constexpr int KB = D / 16, DT = D / 32;   // 16-deep steps and 32-column blocks
+  static constexpr int SR = 1024 / ROWB;           // rows of a 1 KB direct load (slot)
+  static constexpr int TILE = 64 * ROWB;           // bytes of a 64-row tile
+  // tile row and source chunk that this lane loads for slot s
+  static __device__ inline int slot_row(int s, int lane) { return SR * s + lane / CH; }
+  static __device__ inline int slot_chunk(int s, int lane) { return (lane % CH) ^ asw<D>(slot_row(s, lane)); }
+  // byte offsets of the two transposing reads of column block dt for a lane
   static __device__ inline int2 tr_off(int lane, int dt) {
     const int g = lane >> 4, j = lane & 15;
     const int q1 = 4 * (g >> 1) + (j >> 2), q2 = q1 + 8;
     const int ch = 4 * dt + 2 * (g & 1) + ((j & 3) >> 1);
-    return {q1 * 256 + ((ch ^ asw(q1)) << 4) + (j & 1) * 8, q2 * 256 + ((ch ^ asw(q2)) << 4) + (j & 1) * 8};
+    return {q1 * ROWB + ((ch ^ asw<D>(q1)) << 4) + (j & 1) * 8, q2 * ROWB + ((ch ^ asw<D>(q2)) << 4) + (j & 1) * 8};
   }
-  // 16 direct loads of 1 KB (4 rows each), 4 per wave; rowoff(r) = byte offset
-  // of tile row r in the resource, or a negative value for a padding row
-  template <class RowOff>
-  __device__ inline void load(__amdgpu_buffer_rsrc_t R, char* S, RowOff rowoff) const {
+};
+
+// Per-lane constants of one 64-row tile: direct-load slots of a four-wave
+// workgroup and fragment offsets.
+template <int D>
+struct ATile {
+  typedef AGeo<D> G;
+  static constexpr int NL = G::TILE / 4096;  // slots per wave
+  int lrow[NL], lchunk[NL];  // direct loads: tile row and source chunk of this lane, per load
+  int roff[G::KB];           // row fragment, k16 step kb: byte offset for tile row (lane % 32)
+  int t1[G::DT], t2[G::DT];  // transposed fragment, 32-column block dt: the two reads
+  __device__ inline void init() {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < NL; ++t) {
+      lrow[t] = G::slot_row(wave * NL + t, lane);
+      lchunk[t] = G::slot_chunk(wave * NL + t, lane);
+    }
+    const int rr = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int kb = 0; kb < G::KB; ++kb) roff[kb] = rr * G::ROWB + (((2 * kb + h) ^ asw<D>(rr)) << 4);
+#pragma unroll
+    for (int dt = 0; dt < G::DT; ++dt) {
+      const int2 o = G::tr_off(lane, dt);
+      t1[dt] = o.x;
+      t2[dt] = o.y;
+    }
+  }
+  // the tile's direct loads at precomputed byte offsets off[t] (AOOB: a padding row)
+  __device__ inline void load_at(__amdgpu_buffer_rsrc_t R, char* S, const int* off) const {
     // wave-uniform: the LDS destination (M0) is then computed on the scalar unit
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int ro = rowoff(lrow[t]);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(R, ALDS(S + (wave * 4 + t) * 1024), 16, ro < 0 ? AOOB : ro + lchunk[t] * 16,
-                                               0, 0, 0);
-    }
-  }
-  // the same 16 loads with precomputed byte offsets off[t] (AOOB: a padding row)
-  __device__ inline void load_at(__amdgpu_buffer_rsrc_t R, char* S, const int* off) const {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(R, ALDS(S + (wave * 4 + t) * 1024), 16, off[t], 0, 0, 0);
+    for (int t = 0; t < NL; ++t)
+      lds_load<16>(R, S + (wave * NL + t) * 1024, off[t]);
   }
   // A fragment of rows 32t + (lane % 32), elements 16kb + 8(lane / 32) .. +7
   __device__ inline bf16x8 row(const char* S, int t, int kb) const {
-    return __builtin_bit_cast(bf16x8, *(const u32x4*)(S + roff[kb] + t * 8192));
+    return __builtin_bit_cast(bf16x8, *(const u32x4*)(S + roff[kb] + t * 32 * G::ROWB));
   }
   // A fragment of the transposed tile: row d = 32dt + (lane % 32), contraction
   // slots = tile rows 16c + 4(lane / 32) + 0..3 and 16c + 8 + 4(lane / 32) + 0..3
   __device__ inline bf16x8 tr(const char* S, int c, int dt) const {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + t1[dt] + c * 4096));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + t2[dt] + c * 4096));
-    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
-  }
-  // The two read offsets of column block dt, for a dt known only at run time:
-  // recomputed rather than indexed, so that t1/t2 stay in registers (a dynamic
-  // index moves the arrays to LDS and costs a strided LDS read per use)
-  __device__ inline int2 tr_sel(int dt) const { return tr_off(threadIdx.x & 63, dt); }
-  __device__ inline bf16x8 tr(const char* S, int c, int2 o) const {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + o.x + c * 4096));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + o.y + c * 4096));
-    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
+    return tr_pair(S + c * 16 * G::ROWB, t1[dt], t2[dt]);
   }
 };
 
@@ -646,25 +674,15 @@ __device__ __forceinline__ void attn_barrier() {
 // transposing reads of column block dt at t10 ^ (dt << 6), t20 ^ (dt << 6)
 // (the swizzle XORs the 16-byte chunk index, and kb and dt select its upper
 // bits), so one offset per pattern serves all steps.
+template <int D>
 struct ATileX {
   int roff0, t10, t20;
   __device__ inline void init() {
     const int lane = threadIdx.x & 63, rr = lane & 31, h = lane >> 5;
-    roff0 = rr * 256 + ((h ^ asw(rr)) << 4);
-    const int2 o = ATile::tr_off(lane, 0);
+    roff0 = rr * AGeo<D>::ROWB + ((h ^ asw<D>(rr)) << 4);
+    const int2 o = AGeo<D>::tr_off(lane, 0);
     t10 = o.x;
     t20 = o.y;
-  }
-  __device__ inline bf16x8 row(const char* S, int t, int kb) const {
-    return __builtin_bit_cast(bf16x8, *(const u32x4*)(S + (roff0 ^ (kb << 5)) + t * 8192));
-  }
-  __device__ inline bf16x8 tr(const char* S, int c, int dt) const {
-    const s16x4 lo =
-        __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + (t10 ^ (dt << 6)) + c * 4096));
-    const s16x4 hi =
-        __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(S + (t20 ^ (dt << 6)) + c * 4096));
-    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
   }
 };
 
@@ -681,23 +699,25 @@ struct ATileX {
 // past the padded width fall outside the store resource.
 constexpr int KV5_KB = 128, KV5_QT = 64;
 
-template <bool DS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_kv5_k(AttnBwd a) {
+template <int D, bool DS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4))) void attn_bwd_kv5_k(AttnBwd a) {
+  typedef AGeo<D> G;
+  constexpr int VOF = 2 * G::TILE, GOF = G::TILE;  // V behind K, dO behind Q
   // K | V of the block, and per stage Q | dO of a query tile: the second
   // operand of each array sits at a fixed offset from the first, so one
   // offset register per read pattern serves both
-  __shared__ __attribute__((aligned(1024))) char KV[65536], QG0[32768], QG1[32768];
+  __shared__ __attribute__((aligned(1024))) char KV[4 * G::TILE], QG0[2 * G::TILE], QG1[2 * G::TILE];
   __shared__ __attribute__((aligned(256))) float L0[64], D0[64], L1[64], D1[64];
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, c32 = lane & 31;
   const int kg = w & 3, th = w >> 2;  // key group, query half
   const int key = blockIdx.x * KV5_KB + kg * 32 + c32;
   const int N = a.N;
-  const size_t base = (size_t)bh * N * DH;
-  const float sc = rsqrtf((float)DH), scl = sc * LOG2E;
-  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * DH * 2);
-  const __amdgpu_buffer_rsrc_t RV = arsrc((const uint16_t*)a.V + base, (long)N * DH * 2);
-  const __amdgpu_buffer_rsrc_t RQ = arsrc((const uint16_t*)a.Q + base, (long)N * DH * 2);
+  const size_t base = (size_t)bh * N * D;
+  const float sc = rsqrtf((float)D), scl = sc * LOG2E;
+  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * G::ROWB);
+  const __amdgpu_buffer_rsrc_t RV = arsrc((const uint16_t*)a.V + base, (long)N * G::ROWB);
+  const __amdgpu_buffer_rsrc_t RQ = arsrc((const uint16_t*)a.Q + base, (long)N * G::ROWB);
   const __amdgpu_buffer_rsrc_t RG = arsrc(a.dO, (long)a.rm.rows() * a.ld_do * 2);
   const __amdgpu_buffer_rsrc_t RL = arsrc(a.delta + (size_t)a.B * a.H * N + (size_t)bh * N, (long)N * 4);
   const __amdgpu_buffer_rsrc_t RD = arsrc(a.delta + (size_t)bh * N, (long)N * 4);
@@ -705,43 +725,42 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const __amdgpu_buffer_rsrc_t RS =
       arsrc(DS ? (const uint16_t*)a.dS + (size_t)bh * a.nk_pad * a.ld_ds : nullptr, DS ? (long)a.nk_pad * a.ld_ds * 2 : 0);
   const int srow = (blockIdx.x * KV5_KB * a.ld_ds + (kg * 32 + c32) * 64) * 2;
-  ATileX at;  // fragment offsets (the direct-load slots below are for 8 waves)
+  ATileX<D> at;  // fragment offsets (the direct-load slots below are for 8 waves)
   at.init();
 
-  // direct loads for 8 waves: 1 KB slot s holds rows 4s .. 4s+3
-  auto slot_off = [&](int s) {
-    const int row = 4 * s + lane / 16;
-    return int2{row, ((lane % 16) ^ asw(row)) << 4};
-  };
-  // K and V of the block: 32 slots each, 4 per wave
+  // direct loads for 8 waves, in 1 KB slots
+  auto slot_off = [&](int s) { return int2{G::slot_row(s, lane), G::slot_chunk(s, lane) << 4}; };
+  // K and V of the block: slots per wave
+  constexpr int KS = 2 * G::TILE / 8192;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int s = 4 * w + t;
+  for (int t = 0; t < KS; ++t) {
+    const int s = KS * w + t;
     const int2 o = slot_off(s);
-    const int off = (blockIdx.x * KV5_KB + o.x) * (DH * 2) + o.y;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(RK, ALDS(KV + s * 1024), 16, off, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(RV, ALDS(KV + 32768 + s * 1024), 16, off, 0, 0, 0);
+    const int off = (blockIdx.x * KV5_KB + o.x) * G::ROWB + o.y;
+    lds_load<16>(RK, KV + s * 1024, off);
+    lds_load<16>(RV, KV + VOF + s * 1024, off);
   }
-  // query tiles: 16 slots per operand, 2 per wave
+  // query tiles: slots per operand and wave
+  constexpr int QS = G::TILE / 8192;
   const int gofs_t = b * a.rm.nt, gofs_i = a.rm.B * a.rm.nt + b * a.rm.ni - a.rm.nt;
   const int grow = a.ld_do * 2, nt = a.rm.nt;
   auto load_tile = [&](char* Qd, float* Ld, float* Dd, int q0) {
-    char* const Gd = Qd + 16384;
+    char* const Gd = Qd + GOF;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int2 o = slot_off(2 * w + t);
+    for (int t = 0; t < QS; ++t) {
+      const int2 o = slot_off(QS * w + t);
       const int q = q0 + o.x;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(RQ, ALDS(Qd + (2 * w + t) * 1024), 16, q * (DH * 2) + o.y, 0, 0, 0);
-      const int og = q < N ? __mul24(q + (q < nt ? gofs_t : gofs_i), grow) + hd * DH * 2 + o.y : AOOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(RG, ALDS(Gd + (2 * w + t) * 1024), 16, og, 0, 0, 0);
+      lds_load<16>(RQ, Qd + (QS * w + t) * 1024, q * G::ROWB + o.y);
+      const int og = q < N ? __mul24(q + (q < nt ? gofs_t : gofs_i), grow) + hd * G::ROWB + o.y : AOOB;
+      lds_load<16>(RG, Gd + (QS * w + t) * 1024, og);
     }
-    if (w == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(RL, ALDS(Ld), 4, (q0 + lane) * 4, 0, 0, 0);
-    if (w == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(RD, ALDS(Dd), 4, (q0 + lane) * 4, 0, 0, 0);
+    if (w == 0) lds_load<4>(RL, Ld, (q0 + lane) * 4);
+    if (w == 1) lds_load<4>(RD, Dd, (q0 + lane) * 4);
   };
 
-  f32x16 dv[4], dk[4];
+  f32x16 dv[G::DT], dk[G::DT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { dv[i] = zero16(); dk[i] = zero16(); }
+  for (int i = 0; i < G::DT; ++i) { dv[i] = zero16(); dk[i] = zero16(); }
   const int ntile = ((N + KV5_QT - 1) / KV5_QT + 1) & ~1;
   load_tile(QG0, L0, D0, 0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -750,8 +769,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // onto delta and give delta - dP, so that dS = -P (delta - dP) needs no
   // subtraction per element (padding rows: delta = 0, dO = 0, so still 0)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    u32x4* vp = (u32x4*)(KV + 32768) + i * 512 + threadIdx.x;
+  for (int i = 0; i < VOF / 8192; ++i) {
+    u32x4* vp = (u32x4*)(KV + VOF) + i * 512 + threadIdx.x;
     u32x4 x = *vp;
     x ^= 0x80008000u;
     *vp = x;
@@ -775,20 +794,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // arithmetic is redone in each iteration instead of kept in registers
     // across the loop
     const unsigned bq = lds_addr(Qc), bk = lds_addr(KV);
-    unsigned qo = at.roff0 + th * 8192 + bq, ko = at.roff0 + kg * 8192 + bk;
-    unsigned t1 = at.t10 + th * 8192 + bq, t2 = at.t20 + th * 8192 + bq;
+    unsigned qo = at.roff0 + th * 32 * G::ROWB + bq, ko = at.roff0 + kg * 32 * G::ROWB + bk;
+    unsigned t1 = at.t10 + th * 32 * G::ROWB + bq, t2 = at.t20 + th * 32 * G::ROWB + bq;
     asm volatile("" : "+v"(qo), "+v"(ko), "+v"(t1), "+v"(t2));
     // row fragment of k16 step kb at byte cofs of array S (base b)
     auto rowf = [&](const char* S, unsigned b, unsigned o, int kb, int cofs) {
       return __builtin_bit_cast(bf16x8, *(const u32x4*)(S + ((o ^ (kb << 5)) - b) + cofs));
     };
     auto trf = [&](int blk, int dt, int cofs) {
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(Qc + ((t1 ^ (dt << 6)) - bq) + blk * 4096 + cofs));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(Qc + ((t2 ^ (dt << 6)) - bq) + blk * 4096 + cofs));
-      const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      return __builtin_bit_cast(bf16x8, v);
+      const char* S = Qc + blk * 16 * G::ROWB + cofs;
+      return tr_pair(S, (t1 ^ (dt << 6)) - bq, (t2 ^ (dt << 6)) - bq);
     };
     // S and dP of this wave's keys and query half (lane: key column, query
     // rows 32 th + 8(e/4) + 4h + e%4)
@@ -802,9 +817,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       dpt[4 * g + 3] = D4.w;
     }
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
+    for (int kb = 0; kb < G::KB; ++kb) {
       st = mfma(rowf(Qc, bq, qo, kb, 0), rowf(KV, bk, ko, kb, 0), st);
-      dpt = mfma(rowf(Qc, bq, qo, kb, 16384), rowf(KV, bk, ko, kb, 32768), dpt);
+      dpt = mfma(rowf(Qc, bq, qo, kb, GOF), rowf(KV, bk, ko, kb, VOF), dpt);
     }
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -829,13 +844,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const bf16x8 pb = pack8(st, blk), db = pack8(dpt, blk);
       if constexpr (DS) {
         const u32x4 u = __builtin_bit_cast(u32x4, db);
-        const auto s0 = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4{s0[0], s1[0], s0[1], s1[1]}, RS, (int)(so + 32 * blk), 0, 0);
+        const u32x2 s0 = half_swap(u[0], u[2]);
+        const u32x2 s1 = half_swap(u[1], u[3]);
+        store16(RS, u32x4{s0[0], s1[0], s0[1], s1[1]}, (int)(so + 32 * blk));
       }
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        dv[dt] = mfma(trf(blk, dt, 16384), pb, dv[dt]);
+      for (int dt = 0; dt < G::DT; ++dt) {
+        dv[dt] = mfma(trf(blk, dt, GOF), pb, dv[dt]);
         dk[dt] = mfma(trf(blk, dt, 0), db, dk[dt]);
       }
     }
@@ -848,13 +863,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // to waves 0..3 through LDS (dV, then dK), which add them in that order
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  float* const xs = (float*)KV + kg * 4096;  // 16 KB per key group
+  float* const xs = (float*)KV + kg * (G::DT * 1024);  // 4 KB per key group and column block
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     f32x16* acc = pass == 0 ? dv : dk;
     if (th == 1) {
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+      for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           *(float4*)(xs + ((dt * 4 + g) * 64 + lane) * 4) =
@@ -863,7 +878,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
     if (th == 0) {
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+      for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 o = *(const float4*)(xs + ((dt * 4 + g) * 64 + lane) * 4);
@@ -877,7 +892,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   if (th != 0 || key >= N) return;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       bf16x4 vk, vv;
@@ -886,7 +901,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         vk[i] = (__bf16)(dk[dt][4 * g + i] * sc);
         vv[i] = (__bf16)dv[dt][4 * g + i];
       }
-      const size_t off = base + (size_t)key * DH + 32 * dt + 8 * g + 4 * h;
+      const size_t off = base + (size_t)key * D + 32 * dt + 8 * g + 4 * h;
       *(bf16x4*)((uint16_t*)a.dK + off) = vk;
       *(bf16x4*)((uint16_t*)a.dV + off) = vv;
     }
@@ -905,40 +920,43 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 constexpr int F2_QB = 128, F2_KT = 64;
 constexpr float F2_SLACK = 8.f;
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd2_k(AttnFwd a) {
-  __shared__ __attribute__((aligned(1024))) char K0[16384], V0[16384], K1[16384], V1[16384];
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 4))) void attn_fwd2_k(AttnFwd a) {
+  typedef AGeo<D> G;
+  __shared__ __attribute__((aligned(1024))) char K0[G::TILE], V0[G::TILE], K1[G::TILE], V1[G::TILE];
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, c32 = lane & 31;
   const int q = blockIdx.x * F2_QB + w * 32 + c32;  // this lane's query
   const int N = a.N;
-  const size_t base = (size_t)bh * N * DH;
+  const size_t base = (size_t)bh * N * D;
   const uint16_t* Q = (const uint16_t*)a.Q + base;
-  const float sc = rsqrtf((float)DH) * LOG2E;
-  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * DH * 2);
-  const __amdgpu_buffer_rsrc_t RV = arsrc((const uint16_t*)a.V + base, (long)N * DH * 2);
-  ATile at;
+  const float sc = rsqrtf((float)D) * LOG2E;
+  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * G::ROWB);
+  const __amdgpu_buffer_rsrc_t RV = arsrc((const uint16_t*)a.V + base, (long)N * G::ROWB);
+  ATile<D> at;
   at.init();
   // per load slot: byte offset of the lane's chunk in a tile at k0 = 0
-  int koff[4];
+  constexpr int NL = ATile<D>::NL;
+  int koff[NL];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) koff[t] = at.lrow[t] * (DH * 2) + at.lchunk[t] * 16;
+  for (int t = 0; t < NL; ++t) koff[t] = at.lrow[t] * G::ROWB + at.lchunk[t] * 16;
   auto load_tile = [&](char* Kd, char* Vd, int k0) {
-    int o[4];
+    int o[NL];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) o[t] = koff[t] + k0 * (DH * 2);
+    for (int t = 0; t < NL; ++t) o[t] = koff[t] + k0 * G::ROWB;
     at.load_at(RK, Kd, o);
     at.load_at(RV, Vd, o);
   };
 
-  bf16x8 qf[8];
+  bf16x8 qf[G::KB];
 #pragma unroll
-  for (int kb = 0; kb < 8; ++kb) {
-    if (q < N) qf[kb] = ld8(Q + (size_t)q * DH + kb * 16 + h * 8);
+  for (int kb = 0; kb < G::KB; ++kb) {
+    if (q < N) qf[kb] = ld8(Q + (size_t)q * D + kb * 16 + h * 8);
     else qf[kb] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
   }
-  f32x16 o[4];
+  f32x16 o[G::DT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = zero16();
+  for (int i = 0; i < G::DT; ++i) o[i] = zero16();
   float m = -INFINITY, l = 0.f;
 
   const int ntile = (N + F2_KT - 1) / F2_KT, nfull = N / F2_KT;
@@ -961,12 +979,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     f32x16 st[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      bf16x8 fk[8];
+      bf16x8 fk[G::KB];
 #pragma unroll
-      for (int kb = 0; kb < 8; ++kb) fk[kb] = at.row(Kc, t, kb);
+      for (int kb = 0; kb < G::KB; ++kb) fk[kb] = at.row(Kc, t, kb);
       st[t] = mfma(fk[0], qf[0], zero16());
 #pragma unroll
-      for (int kb = 1; kb < 8; ++kb) st[t] = mfma(fk[kb], qf[kb], st[t]);
+      for (int kb = 1; kb < G::KB; ++kb) st[t] = mfma(fk[kb], qf[kb], st[t]);
     }
     // row maximum of the raw scores (the scale is positive)
     float mx = -INFINITY;
@@ -988,7 +1006,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       l *= corr;
       m = mn;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < G::DT; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[i][e] *= corr;
     }
@@ -1004,11 +1022,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
       const bf16x8 pb = pack8(st[cb >> 1], cb & 1);
-      bf16x8 tv[4];
+      bf16x8 tv[G::DT];
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) tv[dt] = at.tr(Vc, cb, dt);
+      for (int dt = 0; dt < G::DT; ++dt) tv[dt] = at.tr(Vc, cb, dt);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) o[dt] = mfma(tv[dt], pb, o[dt]);
+      for (int dt = 0; dt < G::DT; ++dt) o[dt] = mfma(tv[dt], pb, o[dt]);
     }
   };
   using F = std::false_type;
@@ -1028,9 +1046,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   l += __shfl_xor(l, 32, 64);
   if (q >= N) return;
   const float inv = 1.f / l;
-  uint16_t* O = (uint16_t*)a.O + (size_t)row_of_tok_m(a.rm, b, q) * a.ld_o + hd * DH;
+  uint16_t* O = (uint16_t*)a.O + (size_t)row_of_tok_m(a.rm, b, q) * a.ld_o + hd * D;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       bf16x4 v;
@@ -1046,41 +1064,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // key tiles of 64 rows of K and V stream through three LDS stages.
 constexpr int Q2_QB = 128, Q2_KT = 64;
 
+template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_q2_k(AttnBwd a) {
-  __shared__ __attribute__((aligned(1024))) char K0[16384], V0[16384], K1[16384], V1[16384], K2[16384], V2[16384];
+  typedef AGeo<D> G;
+  constexpr int NL = ATile<D>::NL;
+  __shared__ __attribute__((aligned(1024))) char K0[G::TILE], V0[G::TILE], K1[G::TILE], V1[G::TILE], K2[G::TILE],
+      V2[G::TILE];
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, c32 = lane & 31;
   const int q = blockIdx.x * Q2_QB + w * 32 + c32;
   const int N = a.N;
-  const size_t base = (size_t)bh * N * DH;
+  const size_t base = (size_t)bh * N * D;
   const uint16_t* Q = (const uint16_t*)a.Q + base;
-  const float sc = rsqrtf((float)DH), scl = sc * LOG2E;
-  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * DH * 2);
-  const __amdgpu_buffer_rsrc_t RV = arsrc((const uint16_t*)a.V + base, (long)N * DH * 2);
-  ATile at;
+  const float sc = rsqrtf((float)D), scl = sc * LOG2E;
+  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * G::ROWB);
+  const __amdgpu_buffer_rsrc_t RV = arsrc((const uint16_t*)a.V + base, (long)N * G::ROWB);
+  ATile<D> at;
   at.init();
 
-  bf16x8 qf[8], gf[8];
+  bf16x8 qf[G::KB], gf[G::KB];
   const bool qv = q < N;
-  const uint16_t* G = (const uint16_t*)a.dO + (qv ? (size_t)row_of_tok_m(a.rm, b, q) * a.ld_do + hd * DH : 0);
+  const uint16_t* dO = (const uint16_t*)a.dO + (qv ? (size_t)row_of_tok_m(a.rm, b, q) * a.ld_do + hd * D : 0);
 #pragma unroll
-  for (int kb = 0; kb < 8; ++kb) {
+  for (int kb = 0; kb < G::KB; ++kb) {
     if (qv) {
-      qf[kb] = ld8(Q + (size_t)q * DH + kb * 16 + h * 8);
-      gf[kb] = ld8(G + kb * 16 + h * 8);
+      qf[kb] = ld8(Q + (size_t)q * D + kb * 16 + h * 8);
+      gf[kb] = ld8(dO + kb * 16 + h * 8);
     } else {
       qf[kb] = gf[kb] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
     }
   }
   const float L = qv ? a.lse[(size_t)bh * N + q] * LOG2E : INFINITY;
   const float Dl = qv ? a.delta[(size_t)bh * N + q] : 0.f;
-  f32x16 dq[4];
+  f32x16 dq[G::DT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) dq[i] = zero16();
+  for (int i = 0; i < G::DT; ++i) dq[i] = zero16();
 
   auto load_tile = [&](char* Kd, char* Vd, int k0) {
-    at.load(RK, Kd, [&](int r) { return (k0 + r) * (DH * 2); });
-    at.load(RV, Vd, [&](int r) { return (k0 + r) * (DH * 2); });
+    int o[NL];
+#pragma unroll
+    for (int t = 0; t < NL; ++t) o[t] = (k0 + at.lrow[t]) * G::ROWB + at.lchunk[t] * 16;
+    at.load_at(RK, Kd, o);
+    at.load_at(RV, Vd, o);
   };
   const int ntile = (N + Q2_KT - 1) / Q2_KT;
   load_tile(K0, V0, 0);
@@ -1092,7 +1117,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     char* Kc = c == 0 ? K0 : (c == 1 ? K1 : K2);
     char* Vc = c == 0 ? V0 : (c == 1 ? V1 : V2);
     const int k0 = it * Q2_KT;
-    attn_barrier<8>();
+    attn_barrier<2 * NL>();
     if constexpr (!MASK) {
       if constexpr (c == 0) load_tile(K2, V2, k0 + 2 * Q2_KT);
       else if constexpr (c == 1) load_tile(K0, V0, k0 + 2 * Q2_KT);
@@ -1100,9 +1125,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      bf16x8 fk[8], fv[8];
+      bf16x8 fk[G::KB], fv[G::KB];
 #pragma unroll
-      for (int kb = 0; kb < 8; ++kb) {
+      for (int kb = 0; kb < G::KB; ++kb) {
         fk[kb] = at.row(Kc, t, kb);
         fv[kb] = at.row(Vc, t, kb);
       }
@@ -1110,7 +1135,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       f32x16 st = mfma(fk[0], qf[0], zero16());
       f32x16 dpt = mfma(fv[0], gf[0], zero16());
 #pragma unroll
-      for (int kb = 1; kb < 8; ++kb) {
+      for (int kb = 1; kb < G::KB; ++kb) {
         st = mfma(fk[kb], qf[kb], st);
         dpt = mfma(fv[kb], gf[kb], dpt);
       }
@@ -1123,17 +1148,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         dpt[e] = p * (dpt[e] - Dl);
       }
       __builtin_amdgcn_sched_barrier(0);
-      bf16x8 tk[2][4];
+      bf16x8 tk[2][G::DT];
 #pragma unroll
       for (int half = 0; half < 2; ++half)
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) tk[half][dt] = at.tr(Kc, 2 * t + half, dt);
+        for (int dt = 0; dt < G::DT; ++dt) tk[half][dt] = at.tr(Kc, 2 * t + half, dt);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         const bf16x8 db = pack8(dpt, half);
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) dq[dt] = mfma(tk[half][dt], db, dq[dt]);
+        for (int dt = 0; dt < G::DT; ++dt) dq[dt] = mfma(tk[half][dt], db, dq[dt]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1159,13 +1184,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   __builtin_amdgcn_s_waitcnt(0);
   if (!qv) return;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       bf16x4 v;
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = (__bf16)(dq[dt][4 * g + i] * sc);
-      *(bf16x4*)((uint16_t*)a.dQ + base + (size_t)q * DH + 32 * dt + 8 * g + 4 * h) = v;
+      *(bf16x4*)((uint16_t*)a.dQ + base + (size_t)q * D + 32 * dt + 8 * g + 4 * h) = v;
     }
 }
 
@@ -1177,54 +1202,68 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // LDS reads in the same contraction-slot order; dQ^T += K^T dS^T.  No scores
 // are recomputed: the pass is bound by reading dS^T once.  Eight waves, two
 // per SIMD: wave w takes query block w % 4 (32 queries) and head-dimension
-// half w / 4 (two 32-row blocks of dQ^T), so a wave that waits to issue its
+// half w / 4 (32-row blocks of dQ^T: two at D = 128, one at 64), so a wave that waits to issue its
 // direct loads leaves the SIMD to the other wave's fragment reads and MFMAs.
-// Each wave issues two of the sixteen 1 KB loads of each 64 x 128 tile.
+// The 1 KB loads of each tile are dealt evenly to the waves.
 constexpr int Q4_QB = 128, Q4_KT = 64;
 
+template <int D>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_q4_k(AttnBwd a) {
-  __shared__ __attribute__((aligned(1024))) char K0[16384], S0[16384], K1[16384], S1[16384], K2[16384], S2[16384],
-      K3[16384], S3[16384];
+  typedef AGeo<D> G;
+  typedef AGeo<128> GS;              // a dS^T tile row is 128 queries
+  constexpr int KL = G::TILE / 8192; // K slots per wave and tile
+  constexpr int ND = G::DT / 2;      // 32-row blocks of dQ^T per wave
+  __shared__ __attribute__((aligned(1024))) char K0[G::TILE], S0[16384], K1[G::TILE], S1[16384], K2[G::TILE], S2[16384],
+      K3[G::TILE], S3[16384];
   const int bh = blockIdx.y;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, c32 = lane & 31;
   const int qw = w & 3, dh = w >> 2;
   const int qb = blockIdx.x * Q4_QB;
   const int q = qb + qw * 32 + c32;
   const int N = a.N;
-  const size_t base = (size_t)bh * N * DH;
-  const float sc = rsqrtf((float)DH);
-  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * DH * 2);
+  const size_t base = (size_t)bh * N * D;
+  const float sc = rsqrtf((float)D);
+  const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * G::ROWB);
   const __amdgpu_buffer_rsrc_t RS =
       arsrc((const uint16_t*)a.dS + (size_t)bh * a.nk_pad * a.ld_ds, (long)a.nk_pad * a.ld_ds * 2);
-  ATile at;
-  at.init();
-  // direct-load slots of this wave: tile rows 4 (2w + t) + lane / 16, t = 0, 1;
+  // direct-load slots of this wave: KL of K, 2 of dS^T;
   // sof[t]: the slot's byte offset in a tile of the chunked dS^T (a tile row
   // is 128 queries: source chunks 0-7 in the chunk of the block's first 64
   // queries, 8-15 in the next chunk, 16 KB on)
   // kof[t]: the slot's byte offset in a K tile at k0 = 0
-  int sof[2], kof[2];
+  int sof[2], kof[KL];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const int lrow = 4 * (2 * w + t) + lane / 16, lch = (lane % 16) ^ asw(lrow);
-    sof[t] = lrow * 128 + (lch >> 3) * 16384 + (lch & 7) * 16;
-    kof[t] = lrow * (DH * 2) + lch * 16;
+    const int lch = GS::slot_chunk(2 * w + t, lane);
+    sof[t] = GS::slot_row(2 * w + t, lane) * 128 + (lch >> 3) * 16384 + (lch & 7) * 16;
   }
+#pragma unroll
+  for (int t = 0; t < KL; ++t)
+    kof[t] = G::slot_row(KL * w + t, lane) * G::ROWB + G::slot_chunk(KL * w + t, lane) * 16;
   const int nqt = a.ld_ds / 64;
-  const int2 wsel = at.tr_sel(qw), dsel0 = at.tr_sel(2 * dh), dsel1 = at.tr_sel(2 * dh + 1);
-  f32x16 dq[2] = {zero16(), zero16()};
+  // Offsets of the transposing reads, for blocks known only at run time:
+  // computed rather than indexed, so that they stay in registers (a dynamic
+  // index moves the arrays to LDS and costs a strided LDS read per use)
+  const int2 wsel = GS::tr_off(lane, qw);
+  int2 dsel[ND];
+  f32x16 dq[ND];
+#pragma unroll
+  for (int j = 0; j < ND; ++j) {
+    dsel[j] = G::tr_off(lane, ND * dh + j);
+    dq[j] = zero16();
+  }
   auto load_tile = [&](char* Kd, char* Sd, int k0) {
     // K rows at or past N and key blocks past the padded count lie past
     // their resources and read as zeros; keys k0 .. k0+63 lie in key block
     // k0 / 128 of dS^T, rows (k0 % 128) ..
-    const int kpart = k0 * (DH * 2), spart = ((k0 >> 7) * nqt + qb / 64) * 16384 + (k0 & 64) * 128;
+    const int kpart = k0 * G::ROWB, spart = ((k0 >> 7) * nqt + qb / 64) * 16384 + (k0 & 64) * 128;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(RK, ALDS(Kd + (2 * wave + t) * 1024), 16, kpart + kof[t], 0, 0, 0);
+    for (int t = 0; t < KL; ++t)
+      lds_load<16>(RK, Kd + (KL * wave + t) * 1024, kpart + kof[t]);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(RS, ALDS(Sd + (2 * wave + t) * 1024), 16, spart + sof[t], 0, 0, 0);
+      lds_load<16>(RS, Sd + (2 * wave + t) * 1024, spart + sof[t]);
   };
   // Every tile load is issued whether the tile exists or not, so that the
   // issue order (and the waits the compiler derives from it) is the same in
@@ -1241,27 +1280,25 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     char* Sc = c == 0 ? S0 : (c == 1 ? S1 : (c == 2 ? S2 : S3));
     const int k0 = it * Q4_KT;
     // tile it has landed once at most the loads of the two later tiles in
-    // flight (4 direct loads per tile and wave) are outstanding
-    attn_barrier<8>();
+    // flight (KL + 2 direct loads per tile and wave) are outstanding
+    attn_barrier<2 * (KL + 2)>();
     // the stage of tile it+3 was last read in iteration it-1
     if constexpr (c == 0) load_tile(K3, S3, k0 + 3 * Q4_KT);
     else if constexpr (c == 1) load_tile(K0, S0, k0 + 3 * Q4_KT);
     else if constexpr (c == 2) load_tile(K1, S1, k0 + 3 * Q4_KT);
     else load_tile(K2, S2, k0 + 3 * Q4_KT);
-    bf16x8 tk[2][2], ts[2];
-    tk[0][0] = at.tr(Kc, 0, dsel0);
-    tk[0][1] = at.tr(Kc, 0, dsel1);
-    ts[0] = at.tr(Sc, 0, wsel);
+    bf16x8 tk[2][ND], ts[2];
+    auto frags = [&](int cb, int buf) {
+#pragma unroll
+      for (int j = 0; j < ND; ++j) tk[buf][j] = tr_pair(Kc + cb * 16 * G::ROWB, dsel[j].x, dsel[j].y);
+      ts[buf] = tr_pair(Sc + cb * 16 * GS::ROWB, wsel.x, wsel.y);
+    };
+    frags(0, 0);
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
-      const int cur = cb & 1, nxt = cur ^ 1;
-      if (cb + 1 < 4) {
-        tk[nxt][0] = at.tr(Kc, cb + 1, dsel0);
-        tk[nxt][1] = at.tr(Kc, cb + 1, dsel1);
-        ts[nxt] = at.tr(Sc, cb + 1, wsel);
-      }
-      dq[0] = mfma(tk[cur][0], ts[cur], dq[0]);
-      dq[1] = mfma(tk[cur][1], ts[cur], dq[1]);
+      if (cb + 1 < 4) frags(cb + 1, (cb + 1) & 1);
+#pragma unroll
+      for (int j = 0; j < ND; ++j) dq[j] = mfma(tk[cb & 1][j], ts[cb & 1], dq[j]);
     }
   };
   for (int it = 0; it < ntile; it += 4) {
@@ -1273,59 +1310,84 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __builtin_amdgcn_s_waitcnt(0);
   if (q >= N) return;
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < ND; ++j)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       bf16x4 v;
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = (__bf16)(dq[j][4 * g + i] * sc);
-      *(bf16x4*)((uint16_t*)a.dQ + base + (size_t)q * DH + 32 * (2 * dh + j) + 8 * g + 4 * h) = v;
+      *(bf16x4*)((uint16_t*)a.dQ + base + (size_t)q * D + 32 * (ND * dh + j) + 8 * g + 4 * h) = v;
     }
 }
 
 // ============================================================== dispatch
 static bool mfma_ok(int Dh, int dt, const void* O, int ld_o) {
-  return Dh == DH && dt == BF16 && ((uintptr_t)O % 16 == 0) && (ld_o % 8 == 0);
+  return (Dh == 128 || Dh == 64) && dt == BF16 && ((uintptr_t)O % 16 == 0) && (ld_o % 8 == 0);
 }
 
+// Head dim 64: on the vector ALUs (one score at a time per four lanes) the
+// three passes took 134, 167 and 259 us for 8 samples of 333 tokens x 12
+// heads; here 13, 37 and 13.  The register-staged kernels for offsets beyond 32 bits
+// exist for 128 only.
 int attention_fwd_mfma(const AttnFwd& a, hipStream_t s) {
   if (!mfma_ok(a.Dh, a.dt, a.O, a.ld_o)) return -1;
-  dim3 grid((a.N + F_QB - 1) / F_QB, a.B * a.H);
-  const double nn = (double)a.B * a.H * a.N * (double)a.N * DH;
-  const int pi = prof_begin(PROF_ATTN_FWD);
   // the direct-load kernel addresses K and V with 32-bit byte offsets
-  if ((double)a.N * DH * 2.0 * 3 < 2147483000.0)
-    launch(attn_fwd2_k, dim3((a.N + F2_QB - 1) / F2_QB, a.B * a.H), dim3(256), 0u, s, a);
-  else
-    launch(attn_fwd_mfma_k, grid, dim3(256), 0u, s, a);
+  const bool v2 = (double)a.N * a.Dh * 2.0 * 3 < 2147483000.0;
+  if (!v2 && a.Dh != 128) return -1;
+  const dim3 grid((a.N + F2_QB - 1) / F2_QB, a.B * a.H);
+  const double nn = (double)a.B * a.H * a.N * (double)a.N * a.Dh;
+  const int pi = prof_begin(PROF_ATTN_FWD);
+  if (v2 && a.Dh == 128) launch(attn_fwd2_k<128>, grid, dim3(256), 0u, s, a);
+  else if (v2) launch(attn_fwd2_k<64>, grid, dim3(256), 0u, s, a);
+  else launch(attn_fwd_mfma_k, dim3((a.N + F_QB - 1) / F_QB, a.B * a.H), dim3(256), 0u, s, a);
   prof_end(pi, 4.0 * nn);
   JG_CHECK_LAUNCH("attention_fwd_mfma");
   return 0;
 }
 
-int attention_bwd_mfma(const AttnBwd& a, hipStream_t s) {
-  if (!mfma_ok(a.Dh, a.dt, a.dO, a.ld_do) || a.dt_d != BF16 || (uintptr_t)a.O % 16 || a.ld_o % 8) return -1;
-  hipLaunchKernelGGL(attn_delta_mfma_k, dim3((a.rm.rows() + 3) / 4), dim3(256), 0, s, a);
-  JG_CHECK_LAUNCH("attention_delta_mfma");
-  const double nn = (double)a.B * a.H * a.N * (double)a.N * DH;
-  // the direct-load kernels address dO with 32-bit byte offsets
-  const bool v2 = (double)a.rm.rows() * a.ld_do * 2.0 < 2147483000.0 && (double)a.N * DH * 2.0 * 3 < 2147483000.0;
-  // stored dS^T: the geometry the kernels assume, and 32-bit offsets per head
-  // (the dQ pass fetches up to four key tiles past the padded count)
-  const bool ds = a.dS && a.nk_pad == attn_ds_rows(a.N) && a.ld_ds == attn_ds_ld(a.N) &&
-                  (double)(a.nk_pad + 512) * a.ld_ds * 2.0 < 2147483000.0 && (uintptr_t)a.dS % 16 == 0;
-  AttnBwd ak = a;
-  if (!ds) ak.dS = nullptr;
+// The direct-load backward: dS^T stored when it fits (ds), else recomputed.
+template <int D>
+static int bwd_direct(const AttnBwd& a, bool ds, hipStream_t s) {
+  const double nn = (double)a.B * a.H * a.N * (double)a.N * D;
+  const dim3 gkv((a.N + KV5_KB - 1) / KV5_KB, a.B * a.H), gq((a.N + Q4_QB - 1) / Q4_QB, a.B * a.H);
   int pi = prof_begin(PROF_ATTN_BWD_KV);
-  if (v2 && ds) launch(attn_bwd_kv5_k<true>, dim3((a.N + KV5_KB - 1) / KV5_KB, a.B * a.H), dim3(512), 0u, s, ak);
-  else if (v2) launch(attn_bwd_kv5_k<false>, dim3((a.N + KV5_KB - 1) / KV5_KB, a.B * a.H), dim3(512), 0u, s, ak);
-  else launch(attn_bwd_kv_mfma_k, dim3((a.N + KV_KB - 1) / KV_KB, a.B * a.H), dim3(256), 0u, s, a);
+  if (ds) launch(attn_bwd_kv5_k<D, true>, gkv, dim3(512), 0u, s, a);
+  else launch(attn_bwd_kv5_k<D, false>, gkv, dim3(512), 0u, s, a);
   prof_end(pi, 6.0 * nn);
   JG_CHECK_LAUNCH("attention_bwd_kv_mfma");
   pi = prof_begin(PROF_ATTN_BWD_Q);
-  if (v2 && ds) launch(attn_bwd_q4_k, dim3((a.N + Q4_QB - 1) / Q4_QB, a.B * a.H), dim3(512), 0u, s, a);
-  else if (v2) launch(attn_bwd_q2_k, dim3((a.N + Q2_QB - 1) / Q2_QB, a.B * a.H), dim3(256), 0u, s, a);
-  else launch(attn_bwd_q_mfma_k, dim3((a.N + Q_QB - 1) / Q_QB, a.B * a.H), dim3(256), 0u, s, a);
+  if (ds) launch(attn_bwd_q4_k<D>, gq, dim3(512), 0u, s, a);
+  else launch(attn_bwd_q2_k<D>, dim3((a.N + Q2_QB - 1) / Q2_QB, a.B * a.H), dim3(256), 0u, s, a);
+  prof_end(pi, 2.0 * nn);
+  JG_CHECK_LAUNCH("attention_bwd_q_mfma");
+  return 0;
+}
+
+int attention_bwd_mfma(const AttnBwd& a, hipStream_t s) {
+  if (!mfma_ok(a.Dh, a.dt, a.dO, a.ld_do) || a.dt_d != BF16 || (uintptr_t)a.O % 16 || a.ld_o % 8) return -1;
+  // the direct-load kernels address dO with 32-bit byte offsets
+  const bool v2 = (double)a.rm.rows() * a.ld_do * 2.0 < 2147483000.0 && (double)a.N * a.Dh * 2.0 * 3 < 2147483000.0;
+  if (!v2 && a.Dh != 128) return -1;
+  const dim3 gd((a.rm.rows() + 3) / 4);
+  if (a.Dh == 128) hipLaunchKernelGGL(attn_delta_mfma_k<128>, gd, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(attn_delta_mfma_k<64>, gd, dim3(256), 0, s, a);
+  JG_CHECK_LAUNCH("attention_delta_mfma");
+  if (v2) {
+    // stored dS^T: the geometry the kernels assume, and 32-bit offsets per head
+    // (the dQ pass fetches up to four key tiles past the padded count)
+    const bool ds = a.dS && a.nk_pad == attn_ds_rows(a.N) && a.ld_ds == attn_ds_ld(a.N) &&
+                    (double)(a.nk_pad + 512) * a.ld_ds * 2.0 < 2147483000.0 && (uintptr_t)a.dS % 16 == 0;
+    AttnBwd ak = a;
+    if (!ds) ak.dS = nullptr;
+    return a.Dh == 128 ? bwd_direct<128>(ak, ds, s) : bwd_direct<64>(ak, ds, s);
+  }
+  const double nn = (double)a.B * a.H * a.N * (double)a.N * DH;
+  int pi = prof_begin(PROF_ATTN_BWD_KV);
+  launch(attn_bwd_kv_mfma_k, dim3((a.N + KV_KB - 1) / KV_KB, a.B * a.H), dim3(256), 0u, s, a);
+  prof_end(pi, 6.0 * nn);
+  JG_CHECK_LAUNCH("attention_bwd_kv_mfma");
+  pi = prof_begin(PROF_ATTN_BWD_Q);
+  launch(attn_bwd_q_mfma_k, dim3((a.N + Q_QB - 1) / Q_QB, a.B * a.H), dim3(256), 0u, s, a);
   prof_end(pi, 2.0 * nn);
   JG_CHECK_LAUNCH("attention_bwd_q_mfma");
   return 0;

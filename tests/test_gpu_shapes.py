@@ -100,6 +100,17 @@ def test_modulation_batches(B, over):
     check_pass(block(2, 32, 2, 4, 4, act=pk.BF16, grad_dtype=pk.BF16, **over), B, 2, 2e-2)
 
 
+# attention: bf16 head dim 64 and 128 (128-query and 128-key blocks, 64-row tiles) and the fp32-arithmetic kernels (32
+# queries or keys per workgroup, four waves taking every fourth 32-row tile): one tile, one row beyond, several
+@pytest.mark.parametrize("act,head_dim,n_txt,lat_h,lat_w", [
+    (pk.BF16, 64, 3, 4, 4), (pk.BF16, 64, 28, 12, 12), (pk.BF16, 64, 29, 12, 12), (pk.BF16, 64, 65, 16, 16),
+    (pk.BF16, 64, 77, 24, 26), (pk.BF16, 128, 65, 16, 16), (pk.BF16, 32, 9, 6, 8), (pk.BF16, 16, 21, 12, 14),
+    (pk.F32, 16, 28, 4, 4), (pk.F32, 32, 29, 4, 4), (pk.F32, 64, 33, 12, 16), (pk.F32, 128, 77, 10, 12),
+])
+def test_attention_shapes(act, head_dim, n_txt, lat_h, lat_w):
+    check_pass(block(2, head_dim, n_txt, lat_h, lat_w, act=act), 1, 2, 2e-2 if act == pk.BF16 else 1e-4)
+
+
 # group scores: 16-byte and element loads, a last incomplete step, fewer elements than threads; fp64 sums of exact
 # products differ from numpy's by their order only (n <= 3e5: below n 2^-53)
 @pytest.mark.parametrize("n,off", [(5, 0), (8, 0), (4099, 0), (300007, 0), (4099, 1)])
