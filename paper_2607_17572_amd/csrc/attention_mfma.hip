@@ -15,7 +15,7 @@
 //   dQ:       S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T
 // Softmax works in the log2 domain with the hardware exp2; the stored
 // log-sum-exp is in natural-log units of the scaled scores (shared with the
-// VALU kernels).  Ragged sequence lengths are masked (keys >= N get P = 0,
+// fp32-arithmetic kernels).  Ragged sequence lengths are masked (keys >= N get P = 0,
 // padded queries are not written).
 #include "attention.h"
 #include "prof.h"
