@@ -63,6 +63,7 @@ template <>
 struct Raw8<uint16_t> {
   uint4 u;
   __device__ inline void load(const uint16_t* p) { u = *(const uint4*)p; }
+  __device__ inline void store(uint16_t* p) const { *(uint4*)p = u; }
   __device__ inline float operator[](int e) const {
     const uint32_t w = e < 2 ? u.x : (e < 4 ? u.y : (e < 6 ? u.z : u.w));
     return bf2f((e & 1) ? (w >> 16) : (w & 0xffffu));
@@ -74,6 +75,10 @@ struct Raw8<float> {
   __device__ inline void load(const float* p) {
     a = *(const float4*)p;
     b = *(const float4*)(p + 4);
+  }
+  __device__ inline void store(float* p) const {
+    *(float4*)p = a;
+    *(float4*)(p + 4) = b;
   }
   __device__ inline float operator[](int e) const {
     const float4 v = e < 4 ? a : b;
@@ -512,30 +517,39 @@ __global__ __launch_bounds__(256) void ln_mod_fwd_k(const T* __restrict__ x, int
   if (threadIdx.x == 0) { mean[r] = mu; rstd[r] = rs; }
 }
 
-// Hidden sizes that are multiples of 512: one wave per row, 8 consecutive
-// columns per lane and access (lane columns 8 lane + 512 i), the row's mean
-// and variance from wave reductions.
-template <typename T, int NV>
+// Hidden sizes that are multiples of 8: one wave per row, 8 consecutive columns
+// per lane and access (lane columns 8 lane + 512 i), the row's mean and
+// variance from wave reductions.  RAG: D is not NV * 512 (the last run of
+// columns is incomplete); lanes past it hold zeros.
+template <typename T, int NV, bool RAG>
 __global__ __launch_bounds__(256) void ln_mod_fwd_vec_k(const T* __restrict__ x, RowMap rm, int row0, int nrows,
                                                         const float* __restrict__ mt, const float* __restrict__ mi,
                                                         int mod_w, int sh_off, int sc_off, T* __restrict__ a,
-                                                        float* __restrict__ mean, float* __restrict__ rstd) {
-  constexpr int D = NV * 512;
+                                                        float* __restrict__ mean, float* __restrict__ rstd, int Dr) {
+  const int D = RAG ? Dr : NV * 512;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const bool last = !RAG || 8 * lane + 512 * (NV - 1) < D;  // this lane has columns in the last run
   const int rr = blockIdx.x * 4 + w;
   if (rr >= nrows) return;
   const int r = row0 + rr;
   float v[NV * 8];
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) ld8f(x + (size_t)r * D + 8 * lane + 512 * i, v + 8 * i);
+  for (int i = 0; i < NV; ++i) {
+    if (i + 1 < NV || last) {
+      ld8f(x + (size_t)r * D + 8 * lane + 512 * i, v + 8 * i);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[8 * i + e] = 0.f;
+    }
+  }
 #pragma unroll
   for (int e = 0; e < NV * 8; ++e) s += v[e];
   const float mu = wave_sum(s) / D;
   float s2 = 0.f;
 #pragma unroll
   for (int e = 0; e < NV * 8; ++e) {
-    const float dlt = v[e] - mu;
+    const float dlt = e < 8 * (NV - 1) || last ? v[e] - mu : 0.f;
     s2 += dlt * dlt;
   }
   const float var = wave_sum(s2) / D;
@@ -543,6 +557,7 @@ __global__ __launch_bounds__(256) void ln_mod_fwd_vec_k(const T* __restrict__ x,
   const float* m = (is_txt(rm, r) ? mt : mi) + (size_t)sample_of(rm, r) * mod_w;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
+    if (i + 1 == NV && !last) break;
     const int c = 8 * lane + 512 * i;
     float sc[8], sf[8], o[8];
     ld8f(m + sc_off + c, sc);
@@ -562,21 +577,22 @@ int ln_mod_fwd(const void* x, int act_dt, int D, RowMap rm, int row0, int nrows,
                hipStream_t s) {
   if (D > 256 * MAXC) { set_error("ln_mod_fwd: hidden too large"); return 1; }
   if (nrows <= 0) return 0;
-  if (D % 512 == 0 && D <= 3584 && al16(x) && al16(a) && al16(mod_txt) && al16(mod_img) && mod_w % 4 == 0 &&
+  if (D % 8 == 0 && al16(x) && al16(a) && al16(mod_txt) && al16(mod_img) && mod_w % 4 == 0 &&
       sh_off % 4 == 0 && sc_off % 4 == 0) {
     const dim3 grid((unsigned)((nrows + 3) / 4));
-#define LNF(T, NV)                                                                                                \
-  case NV:                                                                                                        \
-    hipLaunchKernelGGL((ln_mod_fwd_vec_k<T, NV>), grid, dim3(256), 0, s, (const T*)x, rm, row0, nrows, mod_txt,  \
-                       mod_img, mod_w, sh_off, sc_off, (T*)a, mean, rstd);                                       \
+#define LNF1(T, NV, RAG)                                                                                              \
+  hipLaunchKernelGGL((ln_mod_fwd_vec_k<T, NV, RAG>), grid, dim3(256), 0, s, (const T*)x, rm, row0, nrows, mod_txt, \
+                     mod_img, mod_w, sh_off, sc_off, (T*)a, mean, rstd, D)
+#define LNF(T, NV)                     \
+  case NV:                             \
+    if (D % 512) LNF1(T, NV, true);    \
+    else LNF1(T, NV, false);           \
     break;
-    if (act_dt == BF16) {
-      switch (D / 512) { LNF(uint16_t, 1) LNF(uint16_t, 2) LNF(uint16_t, 3) LNF(uint16_t, 4) LNF(uint16_t, 5)
-                         LNF(uint16_t, 6) LNF(uint16_t, 7) }
-    } else {
-      switch (D / 512) { LNF(float, 1) LNF(float, 2) LNF(float, 3) LNF(float, 4) LNF(float, 5) LNF(float, 6)
-                         LNF(float, 7) }
-    }
+#define LNF8(T) \
+  switch ((D + 511) / 512) { LNF(T, 1) LNF(T, 2) LNF(T, 3) LNF(T, 4) LNF(T, 5) LNF(T, 6) LNF(T, 7) LNF(T, 8) }
+    if (act_dt == BF16) LNF8(uint16_t) else LNF8(float)
+#undef LNF8
+#undef LNF1
 #undef LNF
     LAUNCH_OK("ln_mod_fwd_vec");
     return 0;
@@ -656,14 +672,17 @@ __global__ __launch_bounds__(256) void ln_mod_bwd_k(const float* __restrict__ dA
 // shift-gradient column sums accumulate in the wave's own LDS row, so a wave
 // keeps under 256 VGPRs and two blocks share a CU.  A block takes LN_ROWS
 // rows, so the many blocks spread evenly over the CUs.  The per-column partial
-// sums of the waves are combined through LDS in wave order.
+// sums of the waves are combined through LDS in wave order.  RAG as in the
+// forward: hidden sizes that are not multiples of 512 took a block per row with
+// block-wide sums, 42 us for 2664 rows of 768 (here 10) and 19 us for 48 rows
+// of 64 (here 6).
 constexpr int LN_W = 4;
-template <typename T, typename TG, int NV>
+template <typename T, typename TG, int NV, bool RAG>
 __global__ __launch_bounds__(64 * LN_W) __attribute__((amdgpu_waves_per_eu(2, 2))) void ln_mod_bwd_vec_k(
     const float* __restrict__ dA, const T* __restrict__ x, Chunks ch, int c0, const float* __restrict__ mean,
     const float* __restrict__ rstd, const float* __restrict__ mt, const float* __restrict__ mi, int mod_w,
-    int sc_off, const TG* gin, float* g, float* __restrict__ psc, float* __restrict__ psh) {
-  constexpr int D = NV * 512;
+    int sc_off, const TG* gin, float* g, float* __restrict__ psc, float* __restrict__ psh, int Dr) {
+  const int D = RAG ? Dr : NV * 512;
   extern __shared__ float red[];  // [LN_W][D] column sums per wave, then [D] factors 1 + scale
   float* const ms = red + LN_W * D;
   const int q = c0 + blockIdx.x;
@@ -673,8 +692,10 @@ __global__ __launch_bounds__(64 * LN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const float* mg = ((r0 < ch.B * ch.nt) ? mt : mi) + (size_t)b * mod_w + sc_off;
   for (int c = threadIdx.x; c < D; c += 64 * LN_W) ms[c] = mg[c] + 1.f;
   float* const sh = red + w * D + 8 * lane;  // this lane's shift sums
+  const bool last = !RAG || 8 * lane + 512 * (NV - 1) < D;  // this lane has columns in the last run
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
+    if (i + 1 == NV && !last) break;
     *(float4*)(sh + 512 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
     *(float4*)(sh + 512 * i + 4) = make_float4(0.f, 0.f, 0.f, 0.f);
   }
@@ -688,6 +709,7 @@ __global__ __launch_bounds__(64 * LN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
     const int r = r0 + rr;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+      if (i + 1 == NV && !last) break;
       xr[i].load(x + (size_t)r * D + 8 * lane + 512 * i);
       ld8f(dA + (size_t)r * D + 8 * lane + 512 * i, da + 8 * i);
     }
@@ -699,6 +721,7 @@ __global__ __launch_bounds__(64 * LN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+      if (i + 1 == NV && !last) break;
       float m[8], t[8];
       ld8f(ms + mo + 512 * i, m);
       ld8f(sh + 512 * i, t);
@@ -717,6 +740,7 @@ __global__ __launch_bounds__(64 * LN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
     const float m1 = wave_sum(s1) / D, m2 = wave_sum(s2) / D;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+      if (i + 1 == NV && !last) break;
       const int c = 8 * lane + 512 * i;
       float m[8], gv[8];
       ld8f(ms + mo + 512 * i, m);
@@ -736,7 +760,8 @@ __global__ __launch_bounds__(64 * LN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   for (int pass = 0; pass < 2; ++pass) {
     if (pass == 1) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) st8f(sh + 512 * i, asc + 8 * i);
+      for (int i = 0; i < NV; ++i)
+        if (i + 1 < NV || last) st8f(sh + 512 * i, asc + 8 * i);
     }
     __syncthreads();
     float* out = (pass == 0 ? psh : psc) + (size_t)q * D;
@@ -763,26 +788,33 @@ int ln_mod_bwd(const float* dA, const void* x, int act_dt, int D, RowMap rm, int
   if (chunk_range(rm, row0, nrows, &c0, &nc, LN_ROWS)) return 1;
   if (nc == 0) return 0;
   Chunks ch{rm.B, rm.nt, rm.ni, LN_ROWS};
-  if (D % 512 == 0 && D <= 3584 && al16(dA) && al16(x) && al16(g) && al16(g_in)) {
+  if (D % 8 == 0 && al16(dA) && al16(x) && al16(g) && al16(g_in)) {
     const size_t lds = (LN_W + 1) * (size_t)D * sizeof(float);
-#define LNB(T, TG, NV)                                                                                         \
-  case NV: {                                                                                                   \
-    auto k = ln_mod_bwd_vec_k<T, TG, NV>;                                                                      \
+#define LNB1(T, TG, NV, RAG)                                                                                   \
+  {                                                                                                            \
+    auto k = ln_mod_bwd_vec_k<T, TG, NV, RAG>;                                                                 \
     if (lds > 65536 &&                                                                                         \
         hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) { \
       set_error("ln_mod_bwd: cannot reserve the row buffers in LDS");                                          \
       return 3;                                                                                                \
     }                                                                                                          \
     hipLaunchKernelGGL(k, dim3(nc), dim3(64 * LN_W), lds, s, dA, (const T*)x, ch, c0, mean, rstd, mod_txt, mod_img, \
-                       mod_w, sc_off, (const TG*)g_in, g, part_scale, part_shift);                              \
-  } break;
+                       mod_w, sc_off, (const TG*)g_in, g, part_scale, part_shift, D);                           \
+  }
+// (at NV = 8 the exact form spills)
+#define LNB(T, TG, NV)                            \
+  case NV:                                        \
+    if (D % 512 || NV == 8) LNB1(T, TG, NV, true) \
+    else LNB1(T, TG, NV, false)                   \
+    break;
 #define LNS(T, TG) \
-  switch (D / 512) { LNB(T, TG, 1) LNB(T, TG, 2) LNB(T, TG, 3) LNB(T, TG, 4) LNB(T, TG, 5) LNB(T, TG, 6) LNB(T, TG, 7) }
+  switch ((D + 511) / 512) { LNB(T, TG, 1) LNB(T, TG, 2) LNB(T, TG, 3) LNB(T, TG, 4) LNB(T, TG, 5) LNB(T, TG, 6) LNB(T, TG, 7) LNB(T, TG, 8) }
     if (act_dt == BF16 && g_in_dt == BF16) LNS(uint16_t, uint16_t)
     else if (act_dt == BF16) LNS(uint16_t, float)
     else LNS(float, float)
 #undef LNS
 #undef LNB
+#undef LNB1
     LAUNCH_OK("ln_mod_bwd_vec");
     return 0;
   }
@@ -1039,24 +1071,26 @@ __global__ void qk_norm_rope_fwd_row_k(const T* __restrict__ proj, int ld, RowMa
                                        T* __restrict__ Qh, T* __restrict__ Kh, T* __restrict__ Vh,
                                        float* __restrict__ rq, float* __restrict__ rk);
 
-// Forward for bf16 and head_dim 128 with 16-byte accesses, one wave per row:
-// per step the wave takes four heads, 16 lanes per head, each lane 4 RoPE
-// pairs (8 consecutive elements).  The rotation of pair p is computed once per
-// row by lane p and handed to the lanes that use it; the RMS sums run over the
-// 16 lanes of a head.
-__global__ __launch_bounds__(256) void qk_norm_rope_fwd8_k(const uint16_t* __restrict__ proj, int ld, RowMap rm,
-                                                           Rope rp, Gains gn, uint16_t* __restrict__ Qh,
-                                                           uint16_t* __restrict__ Kh, uint16_t* __restrict__ Vh,
-                                                           float* __restrict__ rq, float* __restrict__ rk) {
-  constexpr int Dh = 128;
+// Forward with vector accesses, one wave per row: each lane takes 4 RoPE pairs
+// (8 consecutive elements) of a head, Dh / 8 lanes per head, 512 / Dh heads per
+// step.  The rotation of pair p is computed once per row by lane p and handed
+// to the lanes that use it; the RMS sums run over the lanes of a head.  One
+// pair and one head at a time took 15 us for 2664 rows of 12 heads x 64 (here
+// 7) and 12 us for 1332 rows of 8 heads x 64 in fp32 (here 6).
+template <typename T, int Dh>
+__global__ __launch_bounds__(256) void qk_norm_rope_fwd8_k(const T* __restrict__ proj, int ld, RowMap rm, Rope rp,
+                                                           Gains gn, T* __restrict__ Qh, T* __restrict__ Kh,
+                                                           T* __restrict__ Vh, float* __restrict__ rq,
+                                                           float* __restrict__ rk) {
+  constexpr int LPH = Dh / 8, HPS = 64 / LPH;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rm.rows()) return;
-  const int lane = threadIdx.x & 63, hq = lane >> 4, lp = lane & 15, e0 = 8 * lp;
+  const int lane = threadIdx.x & 63, hq = lane / LPH, lp = lane % LPH, e0 = 8 * lp;
   const int H = rp.H, D = H * Dh, N = rm.nt + rm.ni;
   const int st = r < rm.B * rm.nt ? 0 : 1;
   float qg[8], kg[8];
-  ld8f((const uint16_t*)gn.q[st] + e0, qg);
-  ld8f((const uint16_t*)gn.k[st] + e0, kg);
+  ld8f((const T*)gn.q[st] + e0, qg);
+  ld8f((const T*)gn.k[st] + e0, kg);
   int b, j;
   tok_of_row(rm, r, b, j);
   float sn0, cs0;
@@ -1067,16 +1101,17 @@ __global__ __launch_bounds__(256) void qk_norm_rope_fwd8_k(const uint16_t* __res
     cs[k] = __shfl(cs0, 4 * lp + k, 64);
     sn[k] = __shfl(sn0, 4 * lp + k, 64);
   }
-  const uint16_t* pr = proj + (size_t)r * ld + e0;
+  const T* pr = proj + (size_t)r * ld + e0;
   const size_t ob = ((size_t)b * H * N + j) * Dh + e0;  // head h adds h * N * Dh
-  for (int h0 = 0; h0 < H; h0 += 4) {
+  for (int h0 = 0; h0 < H; h0 += HPS) {
     const int h = h0 + hq;
     const bool hv = h < H;
     const int hh = hv ? h : 0;  // lanes past the last head compute on head 0, store nothing
     float x[8], y[8];
     ld8f(pr + hh * Dh, x);
     ld8f(pr + D + hh * Dh, y);
-    const uint4 vv = *(const uint4*)(pr + 2 * D + hh * Dh);
+    Raw8<T> vv;
+    vv.load(pr + 2 * D + hh * Dh);
     float sq = 0.f, sk = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -1084,9 +1119,9 @@ __global__ __launch_bounds__(256) void qk_norm_rope_fwd8_k(const uint16_t* __res
       sk = fmaf(y[e], y[e], sk);
     }
 #pragma unroll
-    for (int m = 8; m > 0; m >>= 1) {
-      sq += __shfl_xor(sq, m, 16);
-      sk += __shfl_xor(sk, m, 16);
+    for (int m = LPH / 2; m > 0; m >>= 1) {
+      sq += __shfl_xor(sq, m, 64);
+      sk += __shfl_xor(sk, m, 64);
     }
     const float riq = rsqrtf(sq / Dh + 1e-6f), rik = rsqrtf(sk / Dh + 1e-6f);
     float oq[8], ok[8];
@@ -1103,7 +1138,7 @@ __global__ __launch_bounds__(256) void qk_norm_rope_fwd8_k(const uint16_t* __res
       const size_t o = ob + (size_t)h * N * Dh;
       st8f(Qh + o, oq);
       st8f(Kh + o, ok);
-      *(uint4*)(Vh + o) = vv;
+      vv.store(Vh + o);
       if (lp == 0) {
         rq[(size_t)r * H + h] = riq;
         rk[(size_t)r * H + h] = rik;
@@ -1112,16 +1147,31 @@ __global__ __launch_bounds__(256) void qk_norm_rope_fwd8_k(const uint16_t* __res
   }
 }
 
+// Head dims and layouts of the vector kernels (8 consecutive elements).
+static bool qk_vec(int Dh, int ld, const Gains& gn) {
+  return (Dh == 16 || Dh == 32 || Dh == 64 || Dh == 128) && ld % 8 == 0 && al16(gn.q[0]) && al16(gn.q[1]) &&
+         al16(gn.k[0]) && al16(gn.k[1]);
+}
+#define QK_DH(M, T)                \
+  switch (rp.Dh) {                 \
+    case 16: M(T, 16); break;      \
+    case 32: M(T, 32); break;      \
+    case 64: M(T, 64); break;      \
+    default: M(T, 128); break;     \
+  }
+
 int qk_norm_rope_fwd(const void* proj, int ld, int act_dt, RowMap rm, Rope rp, Gains gn,
                      void* Qh, void* Kh, void* Vh, float* rinv_q, float* rinv_k, hipStream_t s) {
   if (rp.Dh > 128 || rp.Dh % 4) { set_error("qk_norm_rope: head_dim must be <= 128 and a multiple of 4"); return 1; }
   // RoPE pairs as one access each: even leading dimension, 8-byte aligned bases
   auto al8 = [](const void* p) { return ((uintptr_t)p & 7u) == 0; };
-  if (act_dt == BF16 && rp.Dh == 128 && !(ld & 7) && al16(proj) && al16(Qh) && al16(Kh) && al16(Vh) &&
-      al16(gn.q[0]) && al16(gn.q[1]) && al16(gn.k[0]) && al16(gn.k[1])) {
-    hipLaunchKernelGGL(qk_norm_rope_fwd8_k, dim3((unsigned)((rm.rows() + 3) / 4)), dim3(256), 0, s,
-                       (const uint16_t*)proj, ld, rm, rp, gn, (uint16_t*)Qh, (uint16_t*)Kh, (uint16_t*)Vh, rinv_q,
-                       rinv_k);
+  if (qk_vec(rp.Dh, ld, gn) && al16(proj) && al16(Qh) && al16(Kh) && al16(Vh)) {
+#define QKF(T, DH)                                                                                                  \
+  hipLaunchKernelGGL((qk_norm_rope_fwd8_k<T, DH>), dim3((unsigned)((rm.rows() + 3) / 4)), dim3(256), 0, s, (const T*)proj, \
+                     ld, rm, rp, gn, (T*)Qh, (T*)Kh, (T*)Vh, rinv_q, rinv_k)
+    if (act_dt == BF16) QK_DH(QKF, uint16_t)
+    else QK_DH(QKF, float)
+#undef QKF
     LAUNCH_OK("qk_norm_rope_fwd8");
     return 0;
   }
@@ -1301,21 +1351,20 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd_k(const TD* __restrict__
   }
 }
 
-// The same backward for bf16 operands and head_dim 128 with 16-byte accesses:
-// per step a wave takes four heads of its row, 16 lanes per head, each lane
-// 4 RoPE pairs (8 consecutive elements).  The rotation of pair p is computed
-// once per row by lane p and handed to the lanes that use it; the per-head
-// sums run over the 16 lanes of the head.
-__global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __restrict__ dQh,
-                                                           const uint16_t* __restrict__ dKh,
-                                                           const uint16_t* __restrict__ dVh,
-                                                           const uint16_t* __restrict__ proj, int ld, RowMap rm,
-                                                           Rope rp, Chunks ch, int c0, Gains gn,
+// The same backward with vector accesses: each lane takes 4 RoPE pairs (8
+// consecutive elements) of a head, Dh / 8 lanes per head, 512 / Dh heads per
+// step.  The rotation of pair p is computed once per row by lane p and handed
+// to the lanes that use it; the per-head sums run over the lanes of the head.
+// The pair-at-a-time kernel above took 37 us for 2664 rows of 12 heads x 64
+// (here 13) and 20 us for 1332 rows of 8 heads x 64 in fp32 (here 8).
+template <typename T, int Dh>
+__global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const T* __restrict__ dQh, const T* __restrict__ dKh,
+                                                           const T* __restrict__ dVh, const T* __restrict__ proj,
+                                                           int ld, RowMap rm, Rope rp, Chunks ch, int c0, Gains gn,
                                                            const float* __restrict__ rq, const float* __restrict__ rk,
-                                                           uint16_t* __restrict__ dproj, int ld_d,
-                                                           float* __restrict__ pgain) {
-  constexpr int Dh = 128;
-  __shared__ float red[4][4][2 * Dh];  // [wave][head slot][q gains | k gains]
+                                                           T* __restrict__ dproj, int ld_d, float* __restrict__ pgain) {
+  constexpr int LPH = Dh / 8, HPS = 64 / LPH;
+  __shared__ float red[4 * HPS][2 * Dh];  // [wave, head slot][q gains | k gains]
   const int q = c0 + blockIdx.x;
   int r0, n, b;
   chunk_rows(ch, q, r0, n, b);
@@ -1324,11 +1373,11 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __res
   r0 += sub * QK_SUB;
   n = min(QK_SUB, n - sub * QK_SUB);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int hq = lane >> 4, lp = lane & 15, e0 = 8 * lp;
+  const int hq = lane / LPH, lp = lane % LPH, e0 = 8 * lp;
   const int H = rp.H, D = H * Dh, N = rm.nt + rm.ni;
   float qg[8], kg[8], gq[8], gk[8];
-  ld8f((const uint16_t*)gn.q[st] + e0, qg);
-  ld8f((const uint16_t*)gn.k[st] + e0, kg);
+  ld8f((const T*)gn.q[st] + e0, qg);
+  ld8f((const T*)gn.k[st] + e0, kg);
 #pragma unroll
   for (int e = 0; e < 8; ++e) gq[e] = gk[e] = 0.f;
   constexpr float inv_dh = 1.f / Dh;
@@ -1344,10 +1393,10 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __res
       cs[k] = __shfl(cs0, 4 * lp + k, 64);
       sn[k] = __shfl(sn0, 4 * lp + k, 64);
     }
-    const uint16_t* pr = proj + (size_t)r * ld + e0;
-    uint16_t* dp = dproj + (size_t)r * ld_d + e0;
+    const T* pr = proj + (size_t)r * ld + e0;
+    T* dp = dproj + (size_t)r * ld_d + e0;
     const size_t ob = ((size_t)bb * H * N + j) * Dh + e0;  // head h adds h * N * Dh
-    for (int h0 = 0; h0 < H; h0 += 4) {
+    for (int h0 = 0; h0 < H; h0 += HPS) {
       const int h = h0 + hq;
       const bool hv = h < H;
       const int hh = hv ? h : 0;  // lanes past the last head compute on head 0, store nothing
@@ -1357,7 +1406,8 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __res
       ld8f(dKh + o, ka);
       ld8f(pr + hh * Dh, x);
       ld8f(pr + D + hh * Dh, y);
-      const uint4 vv = *(const uint4*)(dVh + o);
+      Raw8<T> vv;
+      vv.load(dVh + o);
       const float riq = rq[(size_t)r * H + hh], rik = rk[(size_t)r * H + hh];
       // undo the rotation
       float dq[8], dk[8];
@@ -1375,9 +1425,9 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __res
         sk = fmaf(dk[e] * kg[e], y[e], sk);
       }
 #pragma unroll
-      for (int m = 8; m > 0; m >>= 1) {
-        sq += __shfl_xor(sq, m, 16);
-        sk += __shfl_xor(sk, m, 16);
+      for (int m = LPH / 2; m > 0; m >>= 1) {
+        sq += __shfl_xor(sq, m, 64);
+        sk += __shfl_xor(sk, m, 64);
       }
       const float cq = riq * riq * riq * sq * inv_dh, ck = rik * rik * rik * sk * inv_dh;
       float oq[8], ok[8];
@@ -1389,7 +1439,7 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __res
       if (hv) {
         st8f(dp + h * Dh, oq);
         st8f(dp + D + h * Dh, ok);
-        *(uint4*)(dp + 2 * D + h * Dh) = vv;
+        vv.store(dp + 2 * D + h * Dh);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           gq[e] = fmaf(dq[e], x[e] * riq, gq[e]);
@@ -1398,19 +1448,25 @@ __global__ __launch_bounds__(256) void qk_norm_rope_bwd8_k(const uint16_t* __res
       }
     }
   }
-  // gain partials: the 16 head slots of the block (4 waves x 4) added in order
-  float* const rw = &red[wave][hq][0];
-  *(float4*)(rw + e0) = make_float4(gq[0], gq[1], gq[2], gq[3]);
-  *(float4*)(rw + e0 + 4) = make_float4(gq[4], gq[5], gq[6], gq[7]);
-  *(float4*)(rw + Dh + e0) = make_float4(gk[0], gk[1], gk[2], gk[3]);
-  *(float4*)(rw + Dh + e0 + 4) = make_float4(gk[4], gk[5], gk[6], gk[7]);
+  // gain partials: the block's 4 HPS head slots, 16 per thread in order, then
+  // the threads of a column in order
+  float* const rw = red[wave * HPS + hq];
+  st8f(rw + e0, gq);
+  st8f(rw + Dh + e0, gk);
   __syncthreads();
-  const int c = threadIdx.x;  // 256 threads = 2 Dh gain columns
+  const int c = threadIdx.x % (2 * Dh), g = threadIdx.x / (2 * Dh);
   float a = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w)
+  for (int k = 0; k < 16; ++k) a += red[16 * g + k][c];
+  if constexpr (Dh < 128) {
+    __syncthreads();
+    float* const t = red[0];
+    t[threadIdx.x] = a;
+    __syncthreads();
+    if (g != 0) return;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) a += red[w][k][c];
+    for (int k = 1; k < 128 / Dh; ++k) a += t[2 * Dh * k + c];
+  }
   pgain[((size_t)q * QK_PARTS + sub) * 2 * Dh + c] = a;
 }
 
@@ -1428,11 +1484,14 @@ int qk_norm_rope_bwd(const void* dQh, const void* dKh, const void* dVh, int dt_d
   int c0, nc;
   if (chunk_range(rm, 0, rm.rows(), &c0, &nc)) return 1;
   Chunks ch{rm.B, rm.nt, rm.ni, RED_ROWS};
-  if (act_dt == BF16 && dt_d == BF16 && rp.Dh == 128 && !((ld | ld_d) & 7) && al16(dQh) && al16(dKh) && al16(dVh) &&
-      al16(proj) && al16(dproj) && al16(gn.q[0]) && al16(gn.q[1]) && al16(gn.k[0]) && al16(gn.k[1])) {
-    hipLaunchKernelGGL(qk_norm_rope_bwd8_k, dim3(nc, QK_PARTS), dim3(256), 0, s, (const uint16_t*)dQh,
-                       (const uint16_t*)dKh, (const uint16_t*)dVh, (const uint16_t*)proj, ld, rm, rp, ch, c0, gn,
-                       rinv_q, rinv_k, (uint16_t*)dproj, ld_d, part_gain);
+  if (act_dt == dt_d && qk_vec(rp.Dh, ld | ld_d, gn) && al16(dQh) && al16(dKh) && al16(dVh) && al16(proj) &&
+      al16(dproj)) {
+#define QKV(T, DH)                                                                                               \
+  hipLaunchKernelGGL((qk_norm_rope_bwd8_k<T, DH>), dim3(nc, QK_PARTS), dim3(256), 0, s, (const T*)dQh, (const T*)dKh, \
+                     (const T*)dVh, (const T*)proj, ld, rm, rp, ch, c0, gn, rinv_q, rinv_k, (T*)dproj, ld_d, part_gain)
+    if (act_dt == BF16) QK_DH(QKV, uint16_t)
+    else QK_DH(QKV, float)
+#undef QKV
     LAUNCH_OK("qk_norm_rope_bwd8");
     return 0;
   }

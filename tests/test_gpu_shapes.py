@@ -122,3 +122,11 @@ def test_group_score_forms(n, off, dt, W):
     v = [t.double().cpu().numpy() for t in x]
     cos = [float(v[i] @ v[j] / np.sqrt((v[i] @ v[i]) * (v[j] @ v[j]))) for i in range(W) for j in range(i + 1, W)]
     assert abs(ctx.group_score(x) - np.mean(cos)) <= 1e-12
+
+
+# LayerNorm and q/k norm kernels: hidden sizes whose last 512-column run is incomplete, exact, and the widest (4096);
+# every head dim with fewer, as many and more heads than one step of a wave takes (512 / head dim)
+@pytest.mark.parametrize("heads,head_dim", [(3, 16), (33, 16), (16, 32), (21, 32), (9, 64), (12, 64), (5, 128), (32, 128)])
+@pytest.mark.parametrize("act", [pk.F32, pk.BF16])
+def test_norm_widths(heads, head_dim, act):
+    check_pass(block(heads, head_dim, 3, 4, 6, act=act, mlp_hidden=64), 1, 2, 2e-2 if act == pk.BF16 else 1e-4)
