@@ -460,8 +460,8 @@ static int dbl_fwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
   AttnFwd af{A.Qh, A.Kh, A.Vh, A.O, D, A.lse, B, m.H, m.N, m.Dh, m.act, rm};
   TRY(attention_fwd(af, cx.s));
   TRY(fwd2(A.O, D, st[0].o, st[1].o, D, A.y1, D));
-  TRY(gated_residual(A.x_in, A.y1, m.act, D, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 2 * D, A.xm, cx.s));
-  TRY(ln_mod_fwd(A.xm, m.act, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 3 * D, 4 * D, A.a2, A.m2, A.r2, cx.s));
+  TRY(gated_residual_ln(A.x_in, A.y1, m.act, D, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 2 * D, A.xm, 3 * D, 4 * D, A.a2,
+                        A.m2, A.r2, cx.s));
   TRY(fwd2(A.a2, D, st[0].fc1, st[1].fc1, F, A.h, F, EPI_GELU_FWD, A.pre, F));
   TRY(fwd2(A.h, F, st[0].fc2, st[1].fc2, D, A.y2, D));
   TRY(gated_residual(A.xm, A.y2, m.act, D, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 5 * D, A.x_out, cx.s));

@@ -80,6 +80,10 @@ int ln_mod_bwd(const float* dA, const void* x, int act_dt, int D, RowMap rm, int
 int gated_residual(const void* xi, const void* y, int act_dt, int D, int ld_y, RowMap rm, int row0, int nrows,
                    const float* mod_txt, const float* mod_img, int mod_w, int gate_off, void* xo,
                    hipStream_t s);
+// the same followed by LayerNorm + adaLN modulate of xo (one pass over the rows)
+int gated_residual_ln(const void* xi, const void* y, int act_dt, int D, int ld_y, RowMap rm, int row0, int nrows,
+                      const float* mod_txt, const float* mod_img, int mod_w, int gate_off, void* xo, int sh_off,
+                      int sc_off, void* a, float* mean, float* rstd, hipStream_t s);
 // dY = g * gate[b] (act dtype), partials: part_gate = sum g*y, part_bias = sum dY.
 // g is fp32 or, with bf16 activations, bf16 (g_dt).
 int gate_bwd(const void* g, int g_dt, const void* y, int act_dt, int D, RowMap rm, int row0, int nrows,
