@@ -247,6 +247,7 @@ struct Ws {
   float *p1 = nullptr, *p2 = nullptr;
   float* pr = nullptr;  // double block: partials of the reductions on the weight-gradient stream
   float* dmod[2] = {nullptr, nullptr};
+  bool dmvec_set = false;  // dmvec holds a sum (the first modulation backward of a pass overwrites it)
   float *dmvec = nullptr, *dvec = nullptr, *dsh1 = nullptr, *tmp = nullptr;
   float* slpart = nullptr;
   void* gact = nullptr;
@@ -648,6 +649,15 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
                                   ldo, odt, mode, aux ? row(aux, r0[1], ldaux) : nullptr, ldaux);
     return gemm2(a, b, S);
   };
+  // On one stream the block's reductions wait for each other anyway: one launch
+  // of all of them at the end instead of six.
+  RedJob jobs[RED_MAX_JOBS];
+  int njob = 0;
+  auto red = [&](const RedJob* j, int n) {
+    if (cx.side) return reduce_jobs(j, n, cx.fork());
+    for (int i = 0; i < n; ++i) jobs[njob++] = j[i];
+    return 0;
+  };
   // MLP branch: x_out = xm + gate2 * y2
   TRY(gate_bwd(gin, gin_dt, A.y2, act, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 5 * D, W.dY, D, g2a, g2b, S));
   {
@@ -656,7 +666,7 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
       j[s] = per_sample_job(g2a, D, rm, r0[s], nr[s], W.dmod[s], 6 * D, 5 * D);
       j[2 + s] = to_grad_job(g2b, D, c0[s], nc[s], D, G(dth, m, st[s].fc2.b), m.grad, beta);
     }
-    TRY(reduce_jobs(j, 4, cx.fork()));
+    TRY(red(j, 4));
   }
   TRY(wg2(W.dY, D, A.h, F, D, F, st[0].fc2.w, st[1].fc2.w));
   TRY(dg2(W.dY, D, st[0].fc2.w, st[1].fc2.w, F, D, F, W.dbig, F, act, EPI_GELU_BWD, A.pre, F));
@@ -664,7 +674,7 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
   {
     RedJob j[2];
     for (int s = 0; s < 2; ++s) j[s] = to_grad_job(cf1, F, c0[s], nc[s], F, G(dth, m, st[s].fc1.b), m.grad, beta);
-    TRY(reduce_jobs(j, 2, cx.fork()));
+    TRY(red(j, 2));
   }
   TRY(wg2(W.dbig, F, A.a2, D, F, D, st[0].fc1.w, st[1].fc1.w));
   TRY(dg2(W.dbig, F, st[0].fc1.w, st[1].fc1.w, D, F, D, W.dA, D, F32));
@@ -676,7 +686,7 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
       j[2 * s] = per_sample_job(l2a, D, rm, r0[s], nr[s], W.dmod[s], 6 * D, 4 * D, LN_ROWS);
       j[2 * s + 1] = per_sample_job(l2b, D, rm, r0[s], nr[s], W.dmod[s], 6 * D, 3 * D, LN_ROWS);
     }
-    TRY(reduce_jobs(j, 4, cx.fork()));
+    TRY(red(j, 4));
   }
   // attention branch: xm = x + gate1 * y1 (W.dY and W.dbig are rewritten
   // from here on: the fc2 and fc1 weight gradients that read them are done)
@@ -688,7 +698,7 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
       j[s] = per_sample_job(g1a, D, rm, r0[s], nr[s], W.dmod[s], 6 * D, 2 * D);
       j[2 + s] = to_grad_job(g1b, D, c0[s], nc[s], D, G(dth, m, st[s].o.b), m.grad, beta);
     }
-    TRY(reduce_jobs(j, 4, cx.fork()));
+    TRY(red(j, 4));
     // the last modulation sums on that stream: the block's end waits for them
     TRY(cx.mark());
   }
@@ -711,7 +721,7 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
                                  G(dth, m, st[s].kg), m.grad, beta);
       j[3 * s + 2] = to_grad_job(cqkv, 3 * D, c0[s], nc[s], 3 * D, G(dth, m, st[s].qkv.b), m.grad, beta);
     }
-    TRY(reduce_jobs(j, 6, cx.fork()));
+    TRY(red(j, 6));
   }
   TRY(wg2(W.dbig, 3 * D, A.a1, D, 3 * D, D, st[0].qkv.w, st[1].qkv.w));
   TRY(dg2(W.dbig, 3 * D, st[0].qkv.w, st[1].qkv.w, D, 3 * D, D, W.dA, D, F32));
@@ -723,7 +733,12 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
       j[2 * s] = per_sample_job(W.p1, D, rm, r0[s], nr[s], W.dmod[s], 6 * D, D, LN_ROWS);
       j[2 * s + 1] = per_sample_job(W.p2, D, rm, r0[s], nr[s], W.dmod[s], 6 * D, 0, LN_ROWS);
     }
-    TRY(reduce_jobs(j, 4, S));
+    if (cx.side) {
+      TRY(reduce_jobs(j, 4, S));
+    } else {
+      TRY(red(j, 4));
+      TRY(reduce_jobs(jobs, njob, S));
+    }
   }
   // the modulation sums of the two gates and the second LayerNorm
   TRY(cx.wait_mark());
@@ -731,7 +746,8 @@ static int dbl_bwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
   SmallLinGrad mg[2];
   for (int s = 0; s < 2; ++s)
     mg[s] = {W.dmod[s], nullptr, cx.P(st[s].mod.w), G(dth, m, st[s].mod.w), G(dth, m, st[s].mod.b)};
-  TRY(small_linear_bwd(mvec, B, D, mg, 2, m.act, 6 * D, m.grad, beta, W.dmvec, W.slpart, S, true));
+  TRY(small_linear_bwd(mvec, B, D, mg, 2, m.act, 6 * D, m.grad, beta, W.dmvec, W.slpart, S, W.dmvec_set));
+  W.dmvec_set = true;
   TRY(cx.join());  // the next block reuses W.dY and W.dbig
   (void)rowf;
   return 0;
@@ -779,7 +795,8 @@ static int sgl_bwd(const Ctx& cx, int i, const SglAct& A, const float* mvec, int
     TRY(reduce_jobs(j, 2, cx.s));
   }
   const SmallLinGrad mg{W.dmod[0], nullptr, cx.P(L.mod.w), G(dth, m, L.mod.w), G(dth, m, L.mod.b)};
-  TRY(small_linear_bwd(mvec, B, D, &mg, 1, m.act, 3 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, true));
+  TRY(small_linear_bwd(mvec, B, D, &mg, 1, m.act, 3 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, W.dmvec_set));
+  W.dmvec_set = true;
   return 0;
 }
 
@@ -812,7 +829,13 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
   Ctx cx{m, ctx->stream, (const char*)theta, dsize(m.act)};
   // the double-block weight gradients overlap the rest of the pass on a second
   // stream, except while a kernel class is timed (each timed kernel runs alone)
-  if (!prof_armed() && side_stream(ctx)) {
+  // and where the kernels are so short that the forks and joins cost more than
+  // the overlap gives: SIDE_ROWS rows x hidden and less.  Measured without and
+  // with it (us per step): 48 x 64 390 and 550, 1332 x 512 580 and 602, 2664 x
+  // 768 509 and 536, 2604 x 1536 997 and 996; four passes of 4608 x 3072 15.7
+  // and 14.8 ms.
+  constexpr double SIDE_ROWS = 3e6;
+  if (!prof_armed() && (double)B * m.N * m.D > SIDE_ROWS && side_stream(ctx)) {
     cx.side = ctx->side;
     cx.ev_fork = ctx->fork;
     cx.ev_join = ctx->join;
@@ -828,7 +851,6 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
   Saved S;
   plan_saved(m, B, (void*)saved, S);
   const Global& gl = S.g;
-  TRY(fill_zero(W.dmvec, (size_t)B * D * 4, cx.s));
   // the gradient arriving at the last block: the cotangent itself when that
   // block is a double block of a block-only model (its gate and second
   // LayerNorm backward read it in the activation dtype), else W.g
@@ -856,7 +878,8 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
     TRY(reduce_per_sample(W.p1, D, rm, rt, R - rt, W.dmod[0], 2 * D, D, cx.s, LN_ROWS));
     TRY(reduce_per_sample(W.p2, D, rm, rt, R - rt, W.dmod[0], 2 * D, 0, cx.s, LN_ROWS));
     const SmallLinGrad mg{W.dmod[0], nullptr, cx.P(m.fmod.w), G(dth, m, m.fmod.w), G(dth, m, m.fmod.b)};
-    TRY(small_linear_bwd(gl.mvec, B, D, &mg, 1, act, 2 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, true));
+    TRY(small_linear_bwd(gl.mvec, B, D, &mg, 1, act, 2 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, W.dmvec_set));
+    W.dmvec_set = true;
   }
   for (int i = m.c.n_single - 1; i >= 0; --i) {
     SglAct A = S.s[i];

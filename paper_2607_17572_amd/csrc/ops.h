@@ -137,7 +137,7 @@ struct RedJob {
   float beta = 0.f;
   int blk0 = 0;               // first block of the job (set by reduce_jobs)
 };
-constexpr int RED_MAX_JOBS = 8;
+constexpr int RED_MAX_JOBS = 24;  // a double block's
 RedJob per_sample_job(const float* part, int N, RowMap rm, int row0, int nrows, float* out, int out_stride,
                       int out_off, int R = RED_ROWS);
 RedJob to_grad_job(const float* part, int ld, int chunk0, int nchunk, int N, void* g, int g_dt, float beta);

@@ -1781,7 +1781,7 @@ __global__ __launch_bounds__(1024) void reduce_jobs_k(RedJobs js) {
 }
 
 int reduce_jobs(const RedJob* jobs, int n, hipStream_t s) {
-  if (n < 1 || n > RED_MAX_JOBS) { set_error("reduce_jobs: 1..8 jobs"); return 1; }
+  if (n < 1 || n > RED_MAX_JOBS) { set_error("reduce_jobs: too many jobs"); return 1; }
   RedJobs js;
   js.n = n;
   int blk = 0;
