@@ -630,9 +630,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmGroup gg) {
 
 // --------------------------------------------- direct-to-LDS MFMA GEMM
 // BM x BN workgroup tile (each 192 or 256; 128 x 128 and 64 x 64 for products
-// that do not fill the chip with those, two and five workgroups per CU), WM x
-// WN waves (2 x 2; 2 x 4 for 256 x 256, where a second wave per SIMD keeps the MFMAs busy while the other
-// wave stalls issuing its direct loads: 8% faster on that tile, while 4 x 2
+// that do not fill the chip with those, two and five workgroups per CU), KG
+// groups of WM x WN waves that split the k tiles and add their sums through LDS
+// at the end (one; two for few 64 x 64 tiles with a long contraction), WM x WN
+// = 2 x 2 (2 x 4 for 256 x 256, where a second wave per SIMD keeps the MFMAs
+// busy while the other wave stalls issuing its direct loads: 8% faster on that tile, while 4 x 2
 // on 256 x 192 was slower than 2 x 2), 32-deep k tiles through 4 LDS stages,
 // for K a multiple of 32, or any K where both operands are k-strided (rows past
 // K lie past the operands' ends and load as zeros: a weight gradient over 1089
@@ -683,8 +685,8 @@ __device__ __forceinline__ int swz_t(int k) {
 
 // One operand of the direct-to-LDS kernel: ROWS x 32 elements = ROWS * 64 B per
 // k tile = NB direct loads of 1 KB, NL of them by each of the first NLW of the
-// NW waves (the other waves load none of this operand); a wave's MFMAs read WR
-// of the ROWS rows.
+// NW waves of a k group (the other waves load none of this operand); a wave's
+// MFMAs read WR of the ROWS rows.
 template <bool T, int ROWS, int NW, int WR>
 struct DtlOp {
   static constexpr int NB = ROWS / 16;
@@ -698,7 +700,7 @@ struct DtlOp {
   int kmul;      // bytes per unit of k
   int fo[FR > 2 ? FR : 2];  // fragment read offsets (bytes)
   __device__ inline void init(int ld, int row0, int wrow0) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % NW;
 #pragma unroll
     for (int t = 0; t < NL; ++t) {
       const int b = wave * NL + t;  // 1 KB block of the tile
@@ -730,7 +732,7 @@ struct DtlOp {
   // direct loads of the k tile at k0 into the stage at S (byte pointer)
   __device__ inline void load(__amdgpu_buffer_rsrc_t R, char* S, int k0) const {
     // wave-uniform: the LDS destination (M0) is then computed on the scalar unit
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % NW;
     if (!loads(wave)) return;
 #pragma unroll
     for (int t = 0; t < NL; ++t)
@@ -761,17 +763,15 @@ struct DtlOp {
 // global load its epilogue kind needs (old C, GELU input, bias) is issued
 // before the first use, so the load latency is paid once per row of tiles
 // instead of once per 32x32 tile.  Edge tiles take the checked path.
-template <int BM, int BN, int WM, int WN, int EK>
-__device__ __forceinline__ void dtl_epilogue(const GemmArgs& g, f32x16 (&acc)[BM / (32 * WM)][BN / (32 * WN)],
-                                             int m0, int n0, float* T) {
-  constexpr int FM = BM / (32 * WM), FN = BN / (32 * WN), ES = 36, TS = 32 * ES;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+// rbase, cbase: row and column of the wave's first tile.
+template <int FM, int FN, int EK>
+__device__ __forceinline__ void dtl_epilogue(const GemmArgs& g, f32x16 (&acc)[FM][FN], int rbase, int cbase, float* T) {
+  constexpr int ES = 36, TS = 32 * ES;
+  const int lane = threadIdx.x & 63;
   const int h = lane >> 5, c32 = lane & 31;
   const int rr = lane & 31, cc = (lane >> 5) * 16;  // read-back: row rr, columns cc .. cc+15
-  const int rbase = m0 + wm * (BM / WM), cbase = n0 + wn * (BN / WN);
   const bool vec_ok = (g.N % 8 == 0) && (g.epi.ldc % 8 == 0);
-  const bool inner = vec_ok && m0 + BM <= g.M && n0 + BN <= g.N;
+  const bool inner = vec_ok && rbase + 32 * FM <= g.M && cbase + 32 * FN <= g.N;
   const Epi& e = g.epi;
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
@@ -869,20 +869,20 @@ __device__ __forceinline__ void dtl_epilogue(const GemmArgs& g, f32x16 (&acc)[BM
   }
 }
 
-template <bool TA, bool TB, int EK, int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
+template <bool TA, bool TB, int EK, int BM, int BN, int WM, int WN, int KG>
+__global__ __launch_bounds__(64 * WM * WN * KG) void gemm_dtl_kernel(GemmGroup gg) {
   constexpr int BK = 32, NW = WM * WN, FM = BM / (32 * WM), FN = BN / (32 * WN);
   constexpr int SB = BM * 64;  // byte offset of the B tile in a stage
   // bytes per stage (also a wave's epilogue staging: the 192-wide tiles need
   // more than their 24 or 28 KB of operands)
-  constexpr int STG = BM >= 192 ? 32768 : (BM + BN) * 64;
+  constexpr int STG = BM >= 192 ? 32768 : (BM + BN) * 64;  // of one k group
   // one variable per stage: every LDS access names its stage statically, so
   // the compiler can tell the fragment reads of one stage from the direct
   // loads still landing in another and does not wait for the latter
-  __shared__ __attribute__((aligned(1024))) char st0[STG];
-  __shared__ __attribute__((aligned(1024))) char st1[STG];
-  __shared__ __attribute__((aligned(1024))) char st2[STG];
-  __shared__ __attribute__((aligned(1024))) char st3[STG];
+  __shared__ __attribute__((aligned(1024))) char st0[KG * STG];
+  __shared__ __attribute__((aligned(1024))) char st1[KG * STG];
+  __shared__ __attribute__((aligned(1024))) char st2[KG * STG];
+  __shared__ __attribute__((aligned(1024))) char st3[KG * STG];
 
   // the first tiles0 workgroups compute problem 0, the rest problem 1
   const int sel = (int)blockIdx.x >= gg.tiles0 ? 1 : 0;
@@ -892,7 +892,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
   int tm, tn;
   tile_coords(xcd_remap(local, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int wave = threadIdx.x >> 6;
+  // this wave's k group (wave-uniform), and the wave within the group
+  const int grp = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / NW;
+  const int wave = (threadIdx.x >> 6) % NW;
   const int wm = wave / WN, wn = wave % WN;
 
   typedef DtlOp<TA, BM, NW, BM / WM> OpA;
@@ -915,10 +917,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
 
   auto stage = [&](auto ic) -> char* {
     constexpr int c = decltype(ic)::value & 3;
-    if constexpr (c == 0) return st0;
-    else if constexpr (c == 1) return st1;
-    else if constexpr (c == 2) return st2;
-    else return st3;
+    if constexpr (c == 0) return st0 + grp * STG;
+    else if constexpr (c == 1) return st1 + grp * STG;
+    else if constexpr (c == 2) return st2 + grp * STG;
+    else return st3 + grp * STG;
   };
   bf16x8 fa[2][FM], fb[2][FN];
   auto ldfrag = [&](const char* S, int kk, int buf) {
@@ -934,9 +936,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
       for (int j = 0; j < FN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
   };
+  // the group's k tiles are kt0 .. kt0 + nk - 1 of the nkt (the last group may
+  // have fewer than the others, or none)
+  // (a ragged last k tile of two k-strided operands reads zeros past K)
+  const int nkt = (g.K + BK - 1) / BK, nkg = (nkt + KG - 1) / KG;
+  const int kt0 = grp * nkg, nk = KG == 1 ? nkt : max(0, min(nkg, nkt - kt0));
   auto load_tile = [&](char* S, int t) {
-    oa.load(RA, S, t * BK);
-    ob.load(RB, S + SB, t * BK);
+    oa.load(RA, S, (kt0 + t) * BK);
+    ob.load(RB, S + SB, (kt0 + t) * BK);
   };
 
   // prologue: tiles 0, 1, 2 in flight; wait for tile 0
@@ -953,19 +960,17 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  // (a ragged last k tile of two k-strided operands reads zeros past K)
-  const int nk = (g.K + BK - 1) / BK;
   // Every wave loads both operands: A's loads of a k tile go with the first
   // MFMA step, B's with the second.  A wave stalls while the memory pipeline
   // cannot take its next direct load, and with one wave per SIMD the MFMAs
   // stall with it; spread over both steps, the loads cost 3-4% less time in
   // the weight-gradient products.
   constexpr bool SPLIT = OpA::NLW == NW && OpB::NLW == NW;
-  load_tile(st0, 0);
-  load_tile(st1, 1);
-  load_tile(st2, 2);
+  load_tile(st0 + grp * STG, 0);
+  load_tile(st1 + grp * STG, 1);
+  load_tile(st2 + grp * STG, 2);
   tile_barrier();  // tiles 1 and 2 may still fly
-  ldfrag(st0, 0, 0);
+  ldfrag(st0 + grp * STG, 0, 0);
 
   constexpr int RD = (TA ? 2 : 1) * FM + (TB ? 2 : 1) * FN;  // LDS reads per k16 step
   // k tile kt is read from stage kt % 4, tile kt+3 loads into stage (kt+3) % 4
@@ -978,7 +983,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
     // only A's, B's following in step 1
     ldfrag(S, 1, 1);
     char* Sx = stage(std::integral_constant<int, c + 3>());
-    if constexpr (SPLIT) oa.load(RA, Sx, (kt + 3) * BK);
+    if constexpr (SPLIT) oa.load(RA, Sx, (kt0 + kt + 3) * BK);
     else load_tile(Sx, kt + 3);
     mfma_step(0);
     pipe_sched<FM * FN, RD, 0, SPLIT ? OpA::NL : NL>();
@@ -994,7 +999,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
     }
     // step 1, hiding the first fragment reads of tile kt+1
     ldfrag(Sn, 0, 0);
-    if constexpr (SPLIT) ob.load(RB, Sx + SB, (kt + 3) * BK);
+    if constexpr (SPLIT) ob.load(RB, Sx + SB, (kt0 + kt + 3) * BK);
     mfma_step(1);
     pipe_sched<FM * FN, RD, 0, SPLIT ? OpB::NL : 0>();
     __builtin_amdgcn_sched_barrier(0);
@@ -1009,16 +1014,52 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dtl_kernel(GemmGroup gg) {
   if (kt < nk) iter(std::integral_constant<int, 0>(), kt);
   if (kt + 1 < nk) iter(std::integral_constant<int, 1>(), kt + 1);
   if (kt + 2 < nk) iter(std::integral_constant<int, 2>(), kt + 2);
+  // one barrier per iteration: a group with fewer k tiles joins the others' rest
+  if constexpr (KG > 1)
+    for (int i = nk; i < nkg; ++i) __builtin_amdgcn_s_barrier();
   // every direct load has landed and every wave is past its last fragment
   // read before the stages are reused as per-wave epilogue staging
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // per-wave staging: FN 32 x 36 fp32 tiles (at most 18 KB), NW / 4 waves per stage
-  constexpr int TQ = NW / 4, TB_ = STG / TQ;
-  static_assert(FN * 32 * 36 * 4 <= TB_, "epilogue staging exceeds its share of a stage");
-  const int ws = wave / TQ;
-  float* T = (float*)((ws == 0 ? st0 : ws == 1 ? st1 : ws == 2 ? st2 : st3) + (wave % TQ) * TB_);
-  dtl_epilogue<BM, BN, WM, WN, EK>(g, acc, m0, n0, T);
+  const int rb = m0 + wm * (BM / WM), cb = n0 + wn * (BN / WN);
+  auto stn = [&](int i) { return i == 0 ? st0 : i == 1 ? st1 : i == 2 ? st2 : st3; };
+  if constexpr (KG == 1) {
+    // per-wave staging: FN 32 x 36 fp32 tiles (at most 18 KB), NW / 4 waves per stage
+    constexpr int TQ = NW / 4, TB_ = STG / TQ;
+    static_assert(FN * 32 * 36 * 4 <= TB_, "epilogue staging exceeds its share of a stage");
+    dtl_epilogue<FM, FN, EK>(g, acc, rb, cb, (float*)(stn(wave / TQ) + (wave % TQ) * TB_));
+  } else {
+    // the groups after the first hand it their sums, added in group order
+    static_assert(NW == 4 && FM * FN * 4096 * 4 * (KG - 1) <= 4 * KG * STG, "the sums must fit the stages");
+    const int lane = threadIdx.x & 63;
+    constexpr int PW = FM * FN * 4096;  // bytes per wave
+    if (grp > 0) {
+      const int slot = (grp - 1) * NW + wave, per = KG * STG / PW;
+      float* const out = (float*)(stn(slot / per) + slot % per * PW);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) out[((i * FN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
+    }
+    __syncthreads();
+    if (grp == 0) {
+      for (int q = 0; q < KG - 1; ++q) {
+        const int slot = q * NW + wave, per = KG * STG / PW;
+        const float* const in = (const float*)(stn(slot / per) + slot % per * PW);
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] += in[((i * FN + j) * 16 + e) * 64 + lane];
+      }
+    }
+    __syncthreads();
+    static_assert(FN * 32 * 36 * 4 <= STG, "epilogue staging exceeds its share of a stage");
+    if (grp == 0) dtl_epilogue<FM, FN, EK>(g, acc, rb, cb, (float*)stn(wave));
+  }
 }
 
 // ------------------------------------------------------------------ launch
@@ -1079,7 +1120,7 @@ static int launch_mfma(const GemmArgs& g, hipStream_t s) {
   return 0;
 }
 
-template <bool TA, bool TB, int EK, int BM, int BN, int WM = 2, int WN = 2>
+template <bool TA, bool TB, int EK, int BM, int BN, int WM = 2, int WN = 2, int KG = 1>
 static int launch_dtl(const GemmGroup& gr, hipStream_t s) {
   GemmGroup g = gr;
   int tiles = 0;
@@ -1089,16 +1130,26 @@ static int launch_dtl(const GemmGroup& gr, hipStream_t s) {
     tiles += t;
   }
   if (g.np == 1) g.tiles0 = tiles;
-  launch(gemm_dtl_kernel<TA, TB, EK, BM, BN, WM, WN>, dim3(tiles), dim3(64 * WM * WN), 0u, s, g);
+  launch(gemm_dtl_kernel<TA, TB, EK, BM, BN, WM, WN, KG>, dim3(tiles), dim3(64 * WM * WN * KG), 0u, s, g);
   JG_CHECK_LAUNCH("gemm_dtl");
   return 0;
 }
 
 // Tile shapes of the direct-to-LDS kernel.
-enum { DTL_256 = 0, DTL_256x192, DTL_192x256, DTL_192, DTL_128, DTL_64, DTL_SHAPES };
+enum { DTL_256 = 0, DTL_256x192, DTL_192x256, DTL_192, DTL_128, DTL_64, DTL_SHAPES, DTL_64K2 = DTL_SHAPES };
 static const int DTL_BM[DTL_SHAPES] = {256, 256, 192, 192, 128, 64}, DTL_BN[DTL_SHAPES] = {256, 192, 256, 192, 128, 64};
 
 static long tiles_of(const GemmArgs& g, int bm, int bn) { return (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+
+// 64 x 64 tiles with two k groups where the tiles (a shorter contraction's
+// counted by its share) leave CUs free and each has many k tiles: 400 rows x
+// 768, K 3072 (84 tiles) 18.8 -> 15.2 us, 1024 x 1024 over 4000 + 308 rows (256
+// tiles and 256 short ones) 25.5 -> 19.1; at 504 tiles of K 3072 26.9 -> 28.4,
+// at 84 of K 768 no difference.
+static int dtl64(const GemmGroup& g) {
+  const double t = tiles_of(g.p[0], 64, 64) + (g.np > 1 ? (double)tiles_of(g.p[1], 64, 64) * g.p[1].K / g.p[0].K : 0.0);
+  return t <= 300 && g.p[0].K >= 1024 ? DTL_64K2 : DTL_64;
+}
 
 // Tile shape of an input- or weight-gradient group: the one with the least
 // estimated time = rounds of 256 workgroups x tile area / relative tile
@@ -1129,7 +1180,7 @@ static int dtl_shape(const GemmGroup& g) {
     const double t = rounds * DTL_BM[i] * DTL_BN[i] / eff[i];
     if (t < bt * 0.999) { bt = t; best = i; }
   }
-  return best;
+  return best == DTL_64 ? dtl64(g) : best;
 }
 
 template <bool TA, bool TB, int EK>
@@ -1143,15 +1194,18 @@ static int run_dtl(const GemmGroup& g, hipStream_t s, int shape) {
       default: break;
     }
   }
-  if (shape == DTL_64) return launch_dtl<TA, TB, EK, 64, 64>(g, s);
-  return launch_dtl<TA, TB, EK, 128, 128>(g, s);
+  switch (shape) {
+    case DTL_64: return launch_dtl<TA, TB, EK, 64, 64>(g, s);
+    case DTL_64K2: return launch_dtl<TA, TB, EK, 64, 64, 2, 2, 2>(g, s);
+    default: return launch_dtl<TA, TB, EK, 128, 128>(g, s);
+  }
 }
 
-// The direct-to-LDS kernel computes 32-bit byte offsets up to three k tiles
-// past K; they must stay below 2^31.  A ragged last k tile needs both operands
+// The direct-to-LDS kernel computes 32-bit byte offsets up to six k tiles past
+// K (three of prefetch, three of a k group without tiles); they must stay below 2^31.  A ragged last k tile needs both operands
 // k-strided: their rows past K lie past the operands' ends and read as zeros.
 static bool dtl_fits(const GemmArgs& g) {
-  const double kx = (double)g.K + 128.0;
+  const double kx = (double)g.K + 224.0;
   const double ea = 2.0 * (g.ta ? kx * g.lda + g.M : (double)g.M * g.lda + kx);
   const double eb = 2.0 * (g.tb ? kx * g.ldb + g.N : (double)g.N * g.ldb + kx);
   return (g.K % 32 == 0 || (g.ta && g.tb)) && ea < 2147483000.0 && eb < 2147483000.0;
@@ -1225,7 +1279,7 @@ static int mfma_kind(const GemmArgs& g) {
 //     5.7 us against 10.2 and 22.5).
 // The register-staged kernels take K in whole 64-deep tiles; else the
 // direct-to-LDS ones (128 x 128: 0.55 and 0.75).
-enum { FWD_PIPE256 = DTL_SHAPES, FWD_PIPE128 };
+enum { FWD_PIPE256 = DTL_64K2 + 1, FWD_PIPE128 };
 static int fwd_shape(const GemmGroup& g) {
   long t256 = 0, t128 = 0, t64 = 0;
   bool k64 = true;
@@ -1240,7 +1294,7 @@ static int fwd_shape(const GemmGroup& g) {
   const double c256 = k64 ? (double)((t256 + 255) / 256) : 1e300;
   const double c128 = (double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two);
   const double c64 = 0.21 * (double)((t64 + 255) / 256);
-  if (c64 < c128 && c64 < c256) return DTL_64;
+  if (c64 < c128 && c64 < c256) return dtl64(g);
   if (c128 < c256) return k64 ? FWD_PIPE128 : DTL_128;
   return FWD_PIPE256;
 }
@@ -1324,14 +1378,15 @@ int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
 // launch stubs of kernel templates reached only through the shape switch are
 // otherwise not always emitted).
 #define JG_DTL_SMALL(TA, TB, EK)                                                   \
-  template __global__ void gemm_dtl_kernel<TA, TB, EK, 128, 128, 2, 2>(GemmGroup); \
-  template __global__ void gemm_dtl_kernel<TA, TB, EK, 64, 64, 2, 2>(GemmGroup);
+  template __global__ void gemm_dtl_kernel<TA, TB, EK, 128, 128, 2, 2, 1>(GemmGroup); \
+  template __global__ void gemm_dtl_kernel<TA, TB, EK, 64, 64, 2, 2, 1>(GemmGroup);   \
+  template __global__ void gemm_dtl_kernel<TA, TB, EK, 64, 64, 2, 2, 2>(GemmGroup);
 #define JG_DTL(TA, EK)                                                               \
   JG_DTL_SMALL(TA, true, EK)                                                         \
-  template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 256, 2, 4>(GemmGroup); \
-  template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 192, 2, 2>(GemmGroup); \
-  template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 256, 2, 2>(GemmGroup); \
-  template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 192, 2, 2>(GemmGroup);
+  template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 256, 2, 4, 1>(GemmGroup); \
+  template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 192, 2, 2, 1>(GemmGroup); \
+  template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 256, 2, 2, 1>(GemmGroup); \
+  template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 192, 2, 2, 1>(GemmGroup);
 JG_DTL_SMALL(false, false, EK_BIAS) JG_DTL_SMALL(false, false, EK_GELU)
 JG_DTL(false, EK_F32) JG_DTL(false, EK_BF16) JG_DTL(false, EK_DGELU)
 JG_DTL(true, EK_F32) JG_DTL(true, EK_F32_ACC) JG_DTL(true, EK_BF16) JG_DTL(true, EK_BF16_ACC)

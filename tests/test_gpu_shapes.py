@@ -57,8 +57,9 @@ def test_unaligned_bf16_products():
 
 
 # bf16 products of 64 x 64 and 128 x 128 direct-to-LDS tiles and 128 x 128 register-staged ones: one row below, at and
-# above a tile edge, one k tile, ragged k in the weight gradient (rows), K = 96 (not a multiple of 64)
-@pytest.mark.parametrize("rows,n_out,n_in", [(8, 64, 64), (63, 96, 72), (65, 64, 136), (129, 768, 200), (127, 2048, 1024),
+# above a tile edge, one k tile, ragged k in the weight gradient (rows), K = 96 (not a multiple of 64), an odd number of
+# k tiles over two k groups (1057 rows: 34 with a ragged last one; K = 1056: 33)
+@pytest.mark.parametrize("rows,n_out,n_in", [(8, 64, 64), (63, 96, 72), (65, 64, 136), (129, 768, 200), (1057, 72, 96), (200, 1056, 136), (127, 2048, 1024),
                                              (1089, 1536, 768), (2500, 1544, 1536)])
 def test_bf16_product_tiles(rows, n_out, n_in):
     dY = rounded(synth.normal((rows, n_out), 5), torch.bfloat16)
