@@ -21,8 +21,8 @@
 // Rows past N are read from row N - 1 and their probabilities set to 0.
 // 8 heads of 64 x 4 samples, 333 tokens, fp32: forward, dK/dV and dQ took 102,
 // 140 and 158 us on the vector ALUs (four lanes per row, keys staged in LDS),
-// and the row sums of dO O 18 us with one lane per row; here
-// 39, 56, 32 and 4.
+// and the row sums of dO O 18 us with one lane per row; here 39, and 90 for the
+// backward in one launch (56 + 32 + 4 in three).
 #include "attention.h"
 #include "prof.h"
 
@@ -170,38 +170,20 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_k(AttnFwd a) {
   });
 }
 
-// delta[b][h][j] = sum_d dO[j][h D + d] O[j][h D + d]: one wave per row, D / 4
-// lanes per head
+// sum over the row of a row's two halves: lanes c32 and c32 + 32
 template <int D, typename T>
-__global__ __launch_bounds__(256) void attn_delta_f32_k(AttnBwd a) {
-  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= a.rm.rows()) return;
-  const int bt = a.rm.B * a.rm.nt;
-  const int b = r < bt ? r / a.rm.nt : (r - bt) / a.rm.ni;
-  const int j = r < bt ? r % a.rm.nt : a.rm.nt + (r - bt) % a.rm.ni;
-  const T* O = (const T*)a.O + (size_t)r * a.ld_o;
-  const T* G = (const T*)a.dO + (size_t)r * a.ld_do;
-  const int W = a.H * D;
-  for (int c0 = 0; c0 < W; c0 += 256) {
-    const int c = c0 + lane * 4;
-    float s = 0.f;
-    if (c < W) {
-      float x[4], y[4];
-      ld4(O + c, x);
-      ld4(G + c, y);
+__device__ inline float row_dot(const Row<D, T>& a, const Row<D, T>& b) {
+  float s = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s = fmaf(x[i], y[i], s);
-    }
-#pragma unroll
-    for (int o = 1; o < D / 4; o <<= 1) s += __shfl_xor(s, o, 64);
-    if (lane % (D / 4) == 0 && c < W) a.delta[((size_t)b * a.H + c / D) * a.N + j] = s;
-  }
+  for (int i = 0; i < D / 2; ++i) s = fmaf(a.f[i], b.f[i], s);
+  return s + __shfl_xor(s, 32, 64);
 }
 
+// The row sums delta = sum_d dO O are formed where they are needed (per query
+// of a tile, per column), from a row of O beside the row of dO.
 template <int D, typename T>
-__global__ __launch_bounds__(256) void attn_bwd_kv_f32_k(AttnBwd a) {
+__device__ __forceinline__ void bwd_kv_f32(const AttnBwd& a, float* part) {
   constexpr int DT = (D + 31) / 32;
-  __shared__ float part[4 * D * 33];
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H, N = a.N;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, c32 = lane & 31;
   const int key0 = blockIdx.x * 32;
@@ -209,7 +191,6 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_f32_k(AttnBwd a) {
   const T *Q = (const T*)a.Q + base, *K = (const T*)a.K + base, *V = (const T*)a.V + base;
   const T* G = (const T*)a.dO + hd * D;
   const float* lse = a.lse + (size_t)bh * N;
-  const float* delta = a.delta + (size_t)bh * N;
   const float scale = rsqrtf((float)D), sc = scale * LOG2E_F;
   Row<D, T> kr, vr;
   kr.load(K + (size_t)min(key0 + c32, N - 1) * D, h);
@@ -225,12 +206,15 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_f32_k(AttnBwd a) {
     f32x16 p = score<D, T>(x, kr);
     x.load(grow(c32), h);
     f32x16 ds = score<D, T>(x, vr);
+    Row<D, T> o;
+    o.load((const T*)a.O + (size_t)row_of_tok(a.rm, b, min(q0 + c32, N - 1)) * a.ld_o + hd * D, h);
+    const float delta = row_dot<D, T>(x, o);  // of query q0 + c32
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int q = q0 + acc_row(e, h), qc = min(q, N - 1);
       const float pe = q < N ? __builtin_amdgcn_exp2f(fmaf(p[e], sc, -lse[qc] * LOG2E_F)) : 0.f;
       p[e] = pe;
-      ds[e] = pe * (ds[e] - delta[qc]);
+      ds[e] = pe * (ds[e] - __shfl(delta, acc_row(e, h), 64));
     }
     accumulate<D, T>(dv, p, h, c32, grow);
     accumulate<D, T>(dk, ds, h, c32, qrow);
@@ -245,9 +229,8 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_f32_k(AttnBwd a) {
 }
 
 template <int D, typename T>
-__global__ __launch_bounds__(256) void attn_bwd_q_f32_k(AttnBwd a) {
+__device__ __forceinline__ void bwd_q_f32(const AttnBwd& a, float* part) {
   constexpr int DT = (D + 31) / 32;
-  __shared__ float part[4 * D * 33];
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H, N = a.N;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, c32 = lane & 31;
   const int q0 = blockIdx.x * 32, qc = min(q0 + c32, N - 1);
@@ -257,7 +240,9 @@ __global__ __launch_bounds__(256) void attn_bwd_q_f32_k(AttnBwd a) {
   Row<D, T> qr, gr;
   qr.load(Q + (size_t)qc * D, h);
   gr.load((const T*)a.dO + (size_t)row_of_tok(a.rm, b, qc) * a.ld_do + hd * D, h);
-  const float l2 = a.lse[(size_t)bh * N + qc] * LOG2E_F, dl = a.delta[(size_t)bh * N + qc];
+  Row<D, T> o;
+  o.load((const T*)a.O + (size_t)row_of_tok(a.rm, b, qc) * a.ld_o + hd * D, h);
+  const float l2 = a.lse[(size_t)bh * N + qc] * LOG2E_F, dl = row_dot<D, T>(gr, o);
   f32x16 dq[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dq[dt] = zero();
@@ -277,6 +262,15 @@ __global__ __launch_bounds__(256) void attn_bwd_q_f32_k(AttnBwd a) {
   });
 }
 
+// Both passes in one launch (z = 0: dK and dV, 1: dQ): they are independent,
+// and at few tokens neither fills the chip.
+template <int D, typename T>
+__global__ __launch_bounds__(256) void attn_bwd_f32_k(AttnBwd a) {
+  __shared__ float part[4 * D * 33];
+  if (blockIdx.z == 0) bwd_kv_f32<D, T>(a, part);
+  else bwd_q_f32<D, T>(a, part);
+}
+
 // ------------------------------------------------------------------ launch
 template <int D, typename T>
 static void fwd_f32(const AttnFwd& a, hipStream_t s) {
@@ -284,10 +278,7 @@ static void fwd_f32(const AttnFwd& a, hipStream_t s) {
 }
 template <int D, typename T>
 static void bwd_f32(const AttnBwd& a, hipStream_t s) {
-  const dim3 grid((a.N + 31) / 32, a.B * a.H);
-  hipLaunchKernelGGL((attn_delta_f32_k<D, T>), dim3((a.rm.rows() + 3) / 4), dim3(256), 0, s, a);
-  hipLaunchKernelGGL((attn_bwd_kv_f32_k<D, T>), grid, dim3(256), 0, s, a);
-  hipLaunchKernelGGL((attn_bwd_q_f32_k<D, T>), grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL((attn_bwd_f32_k<D, T>), dim3((a.N + 31) / 32, a.B * a.H, 2), dim3(256), 0, s, a);
 }
 
 int attention_fwd_mfma(const AttnFwd& a, hipStream_t s);  // attention_mfma.hip; returns -1 if not applicable

@@ -433,7 +433,8 @@ static int dgrad(const Ctx& cx, const void* dY, int ld_dy, int rows, const void*
 static void* G(void* dth, const Model& m, size_t off) { return (char*)dth + off * dsize(m.grad); }
 
 // -------------------------------------------------------------- forward
-static int dbl_fwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int B) {
+// src (optional): the block's input rows, copied to A.x_in on the way
+static int dbl_fwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int B, const void* src = nullptr) {
   const Model& m = cx.m;
   const int D = m.D, F = m.F;
   const RowMap rm{B, m.nt, m.ni};
@@ -444,7 +445,8 @@ static int dbl_fwd(const Ctx& cx, int i, const DblAct& A, const float* mvec, int
   const auto& st = m.dbl[i];
   const SmallLin mod[2] = {{cx.P(st[0].mod.w), cx.P(st[0].mod.b), A.mod[0]}, {cx.P(st[1].mod.w), cx.P(st[1].mod.b), A.mod[1]}};
   TRY(small_linear_fwd(mvec, B, D, mod, 2, m.act, 6 * D, cx.s));
-  TRY(ln_mod_fwd(A.x_in, m.act, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 0, D, A.a1, A.m1, A.r1, cx.s));
+  TRY(ln_mod_fwd(src ? src : A.x_in, m.act, D, rm, 0, R, A.mod[0], A.mod[1], 6 * D, 0, D, A.a1, A.m1, A.r1, cx.s,
+                 src ? A.x_in : nullptr));
   // the two streams' products of each layer: one grouped launch
   auto fwd2 = [&](void* X, int ldx, const Lin& L0, const Lin& L1, int nout, void* Y, int ldy, int mode = EPI_STORE,
                   void* aux = nullptr, int ldaux = 0) {
@@ -479,9 +481,13 @@ static int sgl_fwd(const Ctx& cx, int i, const SglAct& A, const float* mvec, int
   const SmallLin mod{cx.P(sb.mod.w), cx.P(sb.mod.b), A.mod};
   TRY(small_linear_fwd(mvec, B, D, &mod, 1, m.act, 3 * D, cx.s));
   TRY(ln_mod_fwd(A.x_in, m.act, D, rm, 0, R, A.mod, A.mod, 3 * D, 0, D, A.a, A.m, A.r, cx.s));
-  TRY(lin_fwd(cx, A.a, D, R, sb.in, 0, 3 * D, A.proj, LD));
-  TRY(lin_fwd(cx, A.a, D, R, sb.in, 3 * D, F, (char*)A.cat + D * es, LC, EPI_GELU_FWD, (char*)A.proj + 3 * D * es,
-              LD));
+  // q, k, v and the MLP's first layer in one launch: their tiles share whole
+  // rounds (3072 rows x 3072: 432 + 576 tiles of 256 x 256 are 4 rounds of the
+  // CUs together and 2 + 3 apart; 369 us against 160 + 260)
+  TRY(gemm2(lin_args(cx, A.a, D, R, sb.in, 0, 3 * D, A.proj, LD),
+            lin_args(cx, A.a, D, R, sb.in, 3 * D, F, (char*)A.cat + D * es, LC, EPI_GELU_FWD,
+                     (char*)A.proj + 3 * D * es, LD),
+            cx.s));
   Gains gn{{cx.P(sb.qg), cx.P(sb.qg)}, {cx.P(sb.kg), cx.P(sb.kg)}};
   TRY(qk_norm_rope_fwd(A.proj, LD, m.act, rm, Rope{m.H, m.Dh, m.nt, m.ni, m.gw}, gn, A.Qh, A.Kh, A.Vh, A.rq, A.rk,
                        cx.s));
@@ -523,19 +529,14 @@ static int forward(jagg_ctx* ctx, const void* theta, const void* z, const float*
   const SmallLin t_in{cx.P(m.t_in.w), cx.P(m.t_in.b), gl.h1, gl.sh1}, t_out{cx.P(m.t_out.w), cx.P(m.t_out.b), gl.vec, gl.mvec};
   TRY(small_linear_fwd(gl.temb, B, m.tf, &t_in, 1, m.act, D, cx.s));
   TRY(small_linear_fwd(gl.sh1, B, D, &t_out, 1, m.act, D, cx.s));
-  if (m.c.block_only) {
-    if (hipMemcpyAsync(gl.x0, z, (size_t)R * D * es, hipMemcpyDeviceToDevice, cx.s) != hipSuccess) {
-      set_error("forward: copy of the input token rows failed");
-      return 3;
-    }
-  } else {
+  if (!m.c.block_only) {
     TRY(patchify(z, m.act, B, m.C, m.c.lat_h, m.c.lat_w, m.p, gl.patches, cx.s));
-    TRY(lin_fwd(cx, gl.patches, m.pd, B * m.ni, m.img_in, 0, D, (char*)gl.x0 + (size_t)rt * D * es, D));
     if (hipMemcpyAsync(gl.txt, txt, (size_t)B * m.nt * m.dtxt * es, hipMemcpyDeviceToDevice, cx.s) != hipSuccess) {
       set_error("forward: copy of the text embeddings failed");
       return 3;
     }
-    TRY(lin_fwd(cx, gl.txt, m.dtxt, rt, m.txt_in, 0, D, gl.x0, D));
+    TRY(gemm2(lin_args(cx, gl.txt, m.dtxt, rt, m.txt_in, 0, D, gl.x0, D),
+              lin_args(cx, gl.patches, m.pd, B * m.ni, m.img_in, 0, D, (char*)gl.x0 + (size_t)rt * D * es, D), cx.s));
   }
   const bool keep = SP && !m.c.checkpoint;
   void* x = gl.x0;
@@ -545,7 +546,10 @@ static int forward(jagg_ctx* ctx, const void* theta, const void* z, const float*
     A.x_in = x;
     if (SP) A.x_out = S.d[i].x_out;
     else A.x_out = (pp++ % 2) ? W.xa : W.xb;
-    TRY(dbl_fwd(cx, i, A, gl.mvec, B));
+    // a block-only model: the first block reads z (and keeps a copy), the last
+    // writes the output (the backward needs no other copy of it)
+    if (m.c.block_only && i + 1 == m.c.n_double) A.x_out = v_out;
+    TRY(dbl_fwd(cx, i, A, gl.mvec, B, m.c.block_only && i == 0 ? z : nullptr));
     x = A.x_out;
   }
   for (int i = 0; i < m.c.n_single; ++i) {
@@ -556,13 +560,7 @@ static int forward(jagg_ctx* ctx, const void* theta, const void* z, const float*
     TRY(sgl_fwd(cx, i, A, gl.mvec, B));
     x = A.x_out;
   }
-  if (m.c.block_only) {
-    if (hipMemcpyAsync(v_out, x, (size_t)R * D * es, hipMemcpyDeviceToDevice, cx.s) != hipSuccess) {
-      set_error("forward: copy of the output token rows failed");
-      return 3;
-    }
-    return 0;
-  }
+  if (m.c.block_only) return 0;
   const SmallLin fmod{cx.P(m.fmod.w), cx.P(m.fmod.b), gl.fmod};
   TRY(small_linear_fwd(gl.mvec, B, D, &fmod, 1, m.act, 2 * D, cx.s));
   TRY(ln_mod_fwd(x, m.act, D, rm, rt, R - rt, gl.fmod, gl.fmod, 2 * D, 0, D, gl.fa, gl.fm, gl.fr, cx.s));
@@ -875,8 +873,9 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
     void* xl = m.sgl.empty() ? (m.dbl.empty() ? gl.x0 : S.d.back().x_out) : S.s.back().x_out;
     TRY(ln_mod_bwd(W.dfa, xl, act, D, rm, rt, R - rt, gl.fm, gl.fr, gl.fmod, gl.fmod, 2 * D, D, W.g, F32, W.g, W.p1,
                    W.p2, cx.s));
-    TRY(reduce_per_sample(W.p1, D, rm, rt, R - rt, W.dmod[0], 2 * D, D, cx.s, LN_ROWS));
-    TRY(reduce_per_sample(W.p2, D, rm, rt, R - rt, W.dmod[0], 2 * D, 0, cx.s, LN_ROWS));
+    const RedJob j[2] = {per_sample_job(W.p1, D, rm, rt, R - rt, W.dmod[0], 2 * D, D, LN_ROWS),
+                         per_sample_job(W.p2, D, rm, rt, R - rt, W.dmod[0], 2 * D, 0, LN_ROWS)};
+    TRY(reduce_jobs(j, 2, cx.s));
     const SmallLinGrad mg{W.dmod[0], nullptr, cx.P(m.fmod.w), G(dth, m, m.fmod.w), G(dth, m, m.fmod.b)};
     TRY(small_linear_bwd(gl.mvec, B, D, &mg, 1, act, 2 * D, m.grad, beta, W.dmvec, W.slpart, cx.s, W.dmvec_set));
     W.dmvec_set = true;
@@ -908,16 +907,16 @@ static int vjp(jagg_ctx* ctx, const void* theta, const void* saved, int B, const
   if (!m.c.block_only) {
     // input embeddings (no gradient to the inputs themselves)
     TRY(convert(W.g, F32, W.gact, act, (size_t)R * D, cx.s));
-    int c0, nc;
-    TRY(colsum_partials(W.g, F32, D, D, rm, rt, R - rt, W.p1, cx.s));
-    TRY(chunk_range(rm, rt, R - rt, &c0, &nc));
-    TRY(reduce_to_grad(W.p1, D, c0, nc, D, G(dth, m, m.img_in.b), m.grad, beta, cx.s));
-    TRY(wgrad(cx, (char*)W.gact + (size_t)rt * D * es, D, act, gl.patches, m.pd, B * m.ni, D, m.pd,
-              G(dth, m, m.img_in.w), beta));
-    TRY(colsum_partials(W.g, F32, D, D, rm, 0, rt, W.p1, cx.s));
-    TRY(chunk_range(rm, 0, rt, &c0, &nc));
-    TRY(reduce_to_grad(W.p1, D, c0, nc, D, G(dth, m, m.txt_in.b), m.grad, beta, cx.s));
-    TRY(wgrad(cx, W.gact, D, act, gl.txt, m.dtxt, rt, D, m.dtxt, G(dth, m, m.txt_in.w), beta));
+    int ct, nct, ci, nci;
+    TRY(chunk_range(rm, 0, rt, &ct, &nct));
+    TRY(chunk_range(rm, rt, R - rt, &ci, &nci));
+    TRY(colsum_partials(W.g, F32, D, D, rm, 0, R, W.p1, cx.s));
+    const RedJob j[2] = {to_grad_job(W.p1, D, ct, nct, D, G(dth, m, m.txt_in.b), m.grad, beta),
+                         to_grad_job(W.p1, D, ci, nci, D, G(dth, m, m.img_in.b), m.grad, beta)};
+    TRY(reduce_jobs(j, 2, cx.s));
+    TRY(gemm2(wgrad_args(cx, W.gact, D, act, gl.txt, m.dtxt, rt, D, m.dtxt, G(dth, m, m.txt_in.w), beta),
+              wgrad_args(cx, (char*)W.gact + (size_t)rt * D * es, D, act, gl.patches, m.pd, B * m.ni, D, m.pd,
+                         G(dth, m, m.img_in.w), beta), cx.s));
   }
   (void)nchunk;
   // time MLP: vec = SiLU(temb W1^T + b1) W2^T + b2; modulations read SiLU(vec)

@@ -145,6 +145,7 @@ enum EpiKind {
   EK_BIAS = 4,      // C bf16 = acc + bias
   EK_GELU = 5,      // aux bf16 = acc + bias, C bf16 = gelu(aux)
   EK_DGELU = 6,     // C bf16 = acc * gelu'(aux)
+  EK_BIAS_GELU = 7, // a group: EK_BIAS for its first problem, EK_GELU for its second
 };
 
 __device__ __forceinline__ void unpack8(const u32x4& u, float* f) {
@@ -625,7 +626,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_pipe_kernel(GemmGroup gg) {
     for (int kt = 0; kt < nk; ++kt) iter(std::integral_constant<int, 0>(), kt);
   }
   __syncthreads();
-  mfma_epilogue<BM, BN, WM, WN, EK>(g, acc, m0, n0, lds);
+  if constexpr (EK == EK_BIAS_GELU) {
+    if (sel) mfma_epilogue<BM, BN, WM, WN, EK_GELU>(g, acc, m0, n0, lds);
+    else mfma_epilogue<BM, BN, WM, WN, EK_BIAS>(g, acc, m0, n0, lds);
+  } else {
+    mfma_epilogue<BM, BN, WM, WN, EK>(g, acc, m0, n0, lds);
+  }
 }
 
 // --------------------------------------------- direct-to-LDS MFMA GEMM
@@ -1023,11 +1029,19 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_dtl_kernel(GemmGroup g
   __syncthreads();
   const int rb = m0 + wm * (BM / WM), cb = n0 + wn * (BN / WN);
   auto stn = [&](int i) { return i == 0 ? st0 : i == 1 ? st1 : i == 2 ? st2 : st3; };
+  auto finish = [&](float* T) {
+    if constexpr (EK == EK_BIAS_GELU) {
+      if (sel) dtl_epilogue<FM, FN, EK_GELU>(g, acc, rb, cb, T);
+      else dtl_epilogue<FM, FN, EK_BIAS>(g, acc, rb, cb, T);
+    } else {
+      dtl_epilogue<FM, FN, EK>(g, acc, rb, cb, T);
+    }
+  };
   if constexpr (KG == 1) {
     // per-wave staging: FN 32 x 36 fp32 tiles (at most 18 KB), NW / 4 waves per stage
     constexpr int TQ = NW / 4, TB_ = STG / TQ;
     static_assert(FN * 32 * 36 * 4 <= TB_, "epilogue staging exceeds its share of a stage");
-    dtl_epilogue<FM, FN, EK>(g, acc, rb, cb, (float*)(stn(wave / TQ) + (wave % TQ) * TB_));
+    finish((float*)(stn(wave / TQ) + (wave % TQ) * TB_));
   } else {
     // the groups after the first hand it their sums, added in group order
     static_assert(NW == 4 && FM * FN * 4096 * 4 * (KG - 1) <= 4 * KG * STG, "the sums must fit the stages");
@@ -1058,7 +1072,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_dtl_kernel(GemmGroup g
     }
     __syncthreads();
     static_assert(FN * 32 * 36 * 4 <= STG, "epilogue staging exceeds its share of a stage");
-    if (grp == 0) dtl_epilogue<FM, FN, EK>(g, acc, rb, cb, (float*)stn(wave));
+    if (grp == 0) finish((float*)stn(wave));
   }
 }
 
@@ -1230,7 +1244,7 @@ static int epi_kind(const Epi& e) {
 // The kinds that have kernels, per product: forward products add a bias,
 // input gradients overwrite, weight gradients overwrite or accumulate.
 constexpr bool kind_of_product(bool ta, bool tb, int ek) {
-  return !tb ? !ta && (ek == EK_BIAS || ek == EK_GELU)
+  return !tb ? !ta && (ek == EK_BIAS || ek == EK_GELU || ek == EK_BIAS_GELU)
              : ta ? ek >= EK_F32 && ek <= EK_BF16_ACC : ek == EK_F32 || ek == EK_BF16 || ek == EK_DGELU;
 }
 
@@ -1280,7 +1294,7 @@ static int mfma_kind(const GemmArgs& g) {
 // The register-staged kernels take K in whole 64-deep tiles; else the
 // direct-to-LDS ones (128 x 128: 0.55 and 0.75).
 enum { FWD_PIPE256 = DTL_64K2 + 1, FWD_PIPE128 };
-static int fwd_shape(const GemmGroup& g) {
+static int fwd_shape(const GemmGroup& g, int ek) {
   long t256 = 0, t128 = 0, t64 = 0;
   bool k64 = true;
   for (int p = 0; p < g.np; ++p) {
@@ -1292,7 +1306,10 @@ static int fwd_shape(const GemmGroup& g) {
   const double one = k64 ? 0.49 : 0.55, two = k64 ? 0.62 : 0.75;
   const long rem = t128 % 512;
   const double c256 = k64 ? (double)((t256 + 255) / 256) : 1e300;
-  const double c128 = (double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two);
+  double c128 = (double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two);
+  // the smaller tile pays more for the GELU epilogue: 3072 rows x 12288, K 3072
+  // 260 us on 256 x 256 and 288 on 128 x 128 tiles, 232 and 230 without it
+  if (ek != EK_BIAS) c128 *= 1.1;
   const double c64 = 0.21 * (double)((t64 + 255) / 256);
   if (c64 < c128 && c64 < c256) return dtl64(g);
   if (c128 < c256) return k64 ? FWD_PIPE128 : DTL_128;
@@ -1315,7 +1332,9 @@ static int with_kind(const GemmArgs& g, int ek, F f) {
   typedef std::true_type T;
   typedef std::false_type N;
 #define JG_KIND(E) std::integral_constant<int, E>()
-  if (!g.tb) return ek == EK_BIAS ? f(N(), N(), JG_KIND(EK_BIAS)) : f(N(), N(), JG_KIND(EK_GELU));
+  if (!g.tb)
+    return ek == EK_BIAS ? f(N(), N(), JG_KIND(EK_BIAS))
+                         : ek == EK_GELU ? f(N(), N(), JG_KIND(EK_GELU)) : f(N(), N(), JG_KIND(EK_BIAS_GELU));
   if (!g.ta)
     return ek == EK_F32 ? f(N(), T(), JG_KIND(EK_F32))
                         : ek == EK_BF16 ? f(N(), T(), JG_KIND(EK_BF16)) : f(N(), T(), JG_KIND(EK_DGELU));
@@ -1329,7 +1348,7 @@ static int with_kind(const GemmArgs& g, int ek, F f) {
 }
 
 static int launch_group(const GemmGroup& g, int ek, hipStream_t s, int shape = -1) {
-  if (shape < 0) shape = g.p[0].tb ? dtl_shape(g) : fwd_shape(g);
+  if (shape < 0) shape = g.p[0].tb ? dtl_shape(g) : fwd_shape(g, ek);
   return with_kind(g.p[0], ek, [&](auto ta, auto tb, auto k) {
     return run_group<decltype(ta)::value, decltype(tb)::value, decltype(k)::value>(g, s, shape);
   });
@@ -1358,7 +1377,10 @@ int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   const bool whole = a.M > 0 && a.N > 0 && b.M > 0 && b.N > 0 && a.K >= 0 && b.K >= 0 && a.A && a.B && a.epi.C && b.A &&
                      b.B && b.epi.C;
   const int ek = whole ? mfma_kind(a) : -1, ekb = whole ? mfma_kind(b) : -1;
-  const bool alike = whole && a.ta == b.ta && a.tb == b.tb && ek == ekb;
+  // (a bias product and a bias + GELU product of one contraction length make a
+  // group of their own kind)
+  const bool mixed = ek == EK_BIAS && ekb == EK_GELU && a.K == b.K;
+  const bool alike = whole && a.ta == b.ta && a.tb == b.tb && (ek == ekb || mixed);
   if (!alike || (ek >= 0 && !(dtl_fits(a) && dtl_fits(b)))) {
     int rc = gemm(a, s);
     return rc ? rc : gemm(b, s);
@@ -1369,7 +1391,7 @@ int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   g.p[0] = b.K > a.K ? b : a;
   g.p[1] = b.K > a.K ? a : b;
   const int pi = prof_begin(prof_class(a));
-  const int rc = ek < 0 ? gemm_f32(g, s) : launch_group(g, ek, s);
+  const int rc = ek < 0 ? gemm_f32(g, s) : launch_group(g, mixed ? (int)EK_BIAS_GELU : ek, s);
   prof_end(pi, 2.0 * ((double)a.M * a.N * a.K + (double)b.M * b.N * b.K));
   return rc;
 }
@@ -1387,7 +1409,7 @@ int gemm2(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   template __global__ void gemm_dtl_kernel<TA, true, EK, 256, 192, 2, 2, 1>(GemmGroup); \
   template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 256, 2, 2, 1>(GemmGroup); \
   template __global__ void gemm_dtl_kernel<TA, true, EK, 192, 192, 2, 2, 1>(GemmGroup);
-JG_DTL_SMALL(false, false, EK_BIAS) JG_DTL_SMALL(false, false, EK_GELU)
+JG_DTL_SMALL(false, false, EK_BIAS) JG_DTL_SMALL(false, false, EK_GELU) JG_DTL_SMALL(false, false, EK_BIAS_GELU)
 JG_DTL(false, EK_F32) JG_DTL(false, EK_BF16) JG_DTL(false, EK_DGELU)
 JG_DTL(true, EK_F32) JG_DTL(true, EK_F32_ACC) JG_DTL(true, EK_BF16) JG_DTL(true, EK_BF16_ACC)
 #undef JG_DTL

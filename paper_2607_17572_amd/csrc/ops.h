@@ -64,9 +64,10 @@ int time_embed(const TVals& tv, int B, int F, float* temb, hipStream_t s);
 // ---- LayerNorm (no affine) + adaLN modulate ----
 // a = LN(x) * (1 + scale[b]) + shift[b]; rows [row0, row0 + nrows) of the map.
 // mod_txt / mod_img: fp32 [B][mod_w]; shift at column sh_off, scale at sc_off.
+// copy (optional): also receives the rows themselves.
 int ln_mod_fwd(const void* x, int act_dt, int D, RowMap rm, int row0, int nrows, const float* mod_txt,
                const float* mod_img, int mod_w, int sh_off, int sc_off, void* a, float* mean, float* rstd,
-               hipStream_t s);
+               hipStream_t s, void* copy = nullptr);
 // g[r] = g_in[r] + LN_bwd(dA * (1 + scale)) and partials of sum dA*xhat
 // (-> part_scale) and sum dA (-> part_shift) per chunk of LN_ROWS rows,
 // [chunk][D].  g_in is fp32 (it may be g itself) or, with bf16 activations, bf16.
@@ -112,18 +113,15 @@ int qk_norm_rope_bwd(const void* dQh, const void* dKh, const void* dVh, int dt_d
 // column sums of X[rows][ld] (dtype) over chunks -> part[chunk][N]
 int colsum_partials(const void* X, int dt, int ld, int N, RowMap rm, int row0, int nrows, float* part,
                     hipStream_t s);
-// Per-sample reduction: out[b*out_stride + out_off + c] = sum over chunks of sample b (of the
-// chunks belonging to rows [row0, row0+nrows)) of part[chunk][c].  Overwrites.
-// R: rows per chunk of the partials.
-int reduce_per_sample(const float* part, int N, RowMap rm, int row0, int nrows, float* out, int out_stride,
-                      int out_off, hipStream_t s, int R = RED_ROWS);
 // Whole reduction into a parameter gradient: g[c] = beta*g[c] + sum_chunks part[chunk*ld + c].
 int reduce_to_grad(const float* part, int ld, int chunk0, int nchunk, int N, void* g, int g_dt,
                    float beta, hipStream_t s);
 int chunk_range(RowMap rm, int row0, int nrows, int* c0, int* nc, int R = RED_ROWS);
 
-// A list of independent chunk reductions run as one launch, each job with the
-// arithmetic (and so the bits) of reduce_per_sample or reduce_to_grad.
+// A list of independent chunk reductions run as one launch.  Per sample:
+// out[b*out_stride + out_off + c] = sum over the chunks of sample b (of those
+// belonging to rows [row0, row0+nrows)) of part[chunk][c], R rows per chunk;
+// into a parameter gradient: as reduce_to_grad (the same bits).
 struct RedJob {
   const float* part = nullptr;
   int ld = 0, N = 0;          // partial row stride and columns

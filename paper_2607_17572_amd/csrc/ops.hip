@@ -520,9 +520,10 @@ __global__ __launch_bounds__(256) void ln_mod_fwd_k(const T* __restrict__ x, int
 // Hidden sizes that are multiples of 8: one wave per row, 8 consecutive columns
 // per lane and access (lane columns 8 lane + 512 i), the row's mean and
 // variance from wave reductions.  RAG: D is not NV * 512 (the last run of
-// columns is incomplete); lanes past it hold zeros.  GATED: the row is first
-// formed as xo = x + gate * y (stored, and rounded to its type for what
-// follows), so that the gated residual's pass and launch go and its result is
+// columns is incomplete); lanes past it hold zeros.  MODE LN_COPY: the row is
+// also written to xo (the copy of a model's input that the backward needs).
+// MODE LN_GATED: the row is first formed as xo = x + gate * y (stored, and
+// rounded to its type for what follows), so that the gated residual's pass and launch go and its result is
 // not read back: 9216 rows of 3072 in 50 us, where the two kernels took 29
 // and 29.
 template <typename T>
@@ -531,7 +532,8 @@ struct GatedRow {
   T* xo = nullptr;
   int ld_y = 0, gate_off = 0;
 };
-template <typename T, int NV, bool RAG, bool GATED>
+enum { LN_PLAIN, LN_COPY, LN_GATED };
+template <typename T, int NV, bool RAG, int MODE>
 __global__ __launch_bounds__(256) void ln_mod_fwd_vec_k(const T* __restrict__ x, RowMap rm, int row0, int nrows,
                                                         const float* __restrict__ mt, const float* __restrict__ mi,
                                                         int mod_w, int sh_off, int sc_off, T* __restrict__ a,
@@ -551,7 +553,7 @@ __global__ __launch_bounds__(256) void ln_mod_fwd_vec_k(const T* __restrict__ x,
     if (i + 1 < NV || last) {
       const int c = 8 * lane + 512 * i;
       ld8f(x + (size_t)r * D + c, v + 8 * i);
-      if constexpr (GATED) {
+      if constexpr (MODE == LN_GATED) {
         float yv[8], gt[8];
         ld8f(gr.y + (size_t)r * gr.ld_y + c, yv);
         ld8f(m + gr.gate_off + c, gt);
@@ -560,8 +562,8 @@ __global__ __launch_bounds__(256) void ln_mod_fwd_vec_k(const T* __restrict__ x,
           v[8 * i + e] += gt[e] * yv[e];
           if constexpr (sizeof(T) == 2) v[8 * i + e] = bf2f(f2bf(v[8 * i + e]));
         }
-        st8f(gr.xo + (size_t)r * D + c, v + 8 * i);
       }
+      if constexpr (MODE != LN_PLAIN) st8f(gr.xo + (size_t)r * D + c, v + 8 * i);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[8 * i + e] = 0.f;
@@ -601,13 +603,13 @@ static bool ln_vec(const void* x, int D, const float* mod_txt, const float* mod_
          sc_off % 4 == 0;
 }
 
-template <typename T, bool GATED>
+template <typename T, int MODE>
 static void ln_fwd_vec(const void* x, int D, RowMap rm, int row0, int nrows, const float* mod_txt, const float* mod_img,
                        int mod_w, int sh_off, int sc_off, void* a, float* mean, float* rstd, GatedRow<T> gr,
                        hipStream_t s) {
   const dim3 grid((unsigned)((nrows + 3) / 4));
 #define LNF1(NV, RAG)                                                                                                 \
-  hipLaunchKernelGGL((ln_mod_fwd_vec_k<T, NV, RAG, GATED>), grid, dim3(256), 0, s, (const T*)x, rm, row0, nrows, mod_txt, \
+  hipLaunchKernelGGL((ln_mod_fwd_vec_k<T, NV, RAG, MODE>), grid, dim3(256), 0, s, (const T*)x, rm, row0, nrows, mod_txt, \
                      mod_img, mod_w, sh_off, sc_off, (T*)a, mean, rstd, D, gr)
 #define LNF(NV)                  \
   case NV:                       \
@@ -621,16 +623,22 @@ static void ln_fwd_vec(const void* x, int D, RowMap rm, int row0, int nrows, con
 
 int ln_mod_fwd(const void* x, int act_dt, int D, RowMap rm, int row0, int nrows, const float* mod_txt,
                const float* mod_img, int mod_w, int sh_off, int sc_off, void* a, float* mean, float* rstd,
-               hipStream_t s) {
+               hipStream_t s, void* copy) {
   if (D > 256 * MAXC) { set_error("ln_mod_fwd: hidden too large"); return 1; }
   if (nrows <= 0) return 0;
-  if (ln_vec(x, D, mod_txt, mod_img, mod_w, sh_off, sc_off, a)) {
-    if (act_dt == BF16)
-      ln_fwd_vec<uint16_t, false>(x, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd, {}, s);
-    else
-      ln_fwd_vec<float, false>(x, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd, {}, s);
+  if (ln_vec(x, D, mod_txt, mod_img, mod_w, sh_off, sc_off, a) && al16(copy)) {
+#define LNM(T, M, ...) \
+  ln_fwd_vec<T, M>(x, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd, {__VA_ARGS__}, s)
+    if (act_dt == BF16) copy ? LNM(uint16_t, LN_COPY, nullptr, (uint16_t*)copy) : LNM(uint16_t, LN_PLAIN);
+    else copy ? LNM(float, LN_COPY, nullptr, (float*)copy) : LNM(float, LN_PLAIN);
+#undef LNM
     LAUNCH_OK("ln_mod_fwd_vec");
     return 0;
+  }
+  if (copy && hipMemcpyAsync((char*)copy + (size_t)row0 * D * dsize(act_dt), (const char*)x + (size_t)row0 * D * dsize(act_dt),
+                             (size_t)nrows * D * dsize(act_dt), hipMemcpyDeviceToDevice, s) != hipSuccess) {
+    set_error("ln_mod_fwd: copy of the input rows failed");
+    return 3;
   }
   if (act_dt == BF16)
     hipLaunchKernelGGL(ln_mod_fwd_k<uint16_t>, dim3(nrows), dim3(256), 0, s, (const uint16_t*)x, D, rm, row0,
@@ -933,10 +941,10 @@ int gated_residual_ln(const void* xi, const void* y, int act_dt, int D, int ld_y
   if (nrows > 0 && D <= 256 * MAXC && ln_vec(xi, D, mod_txt, mod_img, mod_w, sh_off, sc_off, a) && ld_y % 8 == 0 &&
       al16(y) && al16(xo) && gate_off % 4 == 0) {
     if (act_dt == BF16)
-      ln_fwd_vec<uint16_t, true>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
+      ln_fwd_vec<uint16_t, LN_GATED>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
                                  {(const uint16_t*)y, (uint16_t*)xo, ld_y, gate_off}, s);
     else
-      ln_fwd_vec<float, true>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
+      ln_fwd_vec<float, LN_GATED>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
                               {(const float*)y, (float*)xo, ld_y, gate_off}, s);
     LAUNCH_OK("gated_residual_ln");
     return 0;
@@ -1639,39 +1647,6 @@ __device__ inline float slice_total(float acc, float (*sh)[RC_COLS + 1]) {
   return t;
 }
 
-__global__ __launch_bounds__(1024) void reduce_per_sample_k(const float* __restrict__ part, int N, Chunks ch, int c0,
-                                                            int nc, float* __restrict__ out, int out_stride,
-                                                            int out_off) {
-  __shared__ float sh[RC_SL][RC_COLS + 1];
-  const int b = blockIdx.y;
-  const int cl = threadIdx.x % RC_COLS, sl = threadIdx.x / RC_COLS;
-  const int c = blockIdx.x * RC_COLS + cl;
-  const int ct = ch.ct(), ci = ch.ci();
-  const int runs[2][2] = {{b * ct, b * ct + ct}, {ch.B * ct + b * ci, ch.B * ct + b * ci + ci}};
-  float acc = 0.f;
-  if (c < N)
-    for (int r = 0; r < 2; ++r) {
-      const int lo = max(runs[r][0], c0), hi = min(runs[r][1], c0 + nc);
-#pragma unroll 4
-      for (int q = lo + sl; q < hi; q += RC_SL) acc += part[(size_t)q * N + c];
-    }
-  const float t = slice_total(acc, sh);
-  if (sl == 0 && c < N) out[(size_t)b * out_stride + out_off + c] = t;
-}
-
-int reduce_per_sample(const float* part, int N, RowMap rm, int row0, int nrows, float* out, int out_stride,
-                      int out_off, hipStream_t s, int R) {
-  int c0, nc;
-  if (chunk_range(rm, row0, nrows, &c0, &nc, R)) return 1;
-  Chunks ch{rm.B, rm.nt, rm.ni, R};
-  hipLaunchKernelGGL(reduce_per_sample_k, dim3((N + RC_COLS - 1) / RC_COLS, rm.B), dim3(RC_COLS * RC_SL), 0, s, part,
-                     N, ch, c0, nc, out, out_stride, out_off);
-  LAUNCH_OK("reduce_per_sample");
-  return 0;
-}
-
-// g[c] (+)= sum over chunks [chunk0, chunk0 + nchunk) of part[q * ld + c];
-// beta * g is added once, after the slices.
 template <typename TG>
 __global__ __launch_bounds__(1024) void reduce_to_grad_k(const float* __restrict__ part, int ld, int chunk0,
                                                          int nchunk, int N, TG* __restrict__ g, float beta) {
@@ -1739,7 +1714,7 @@ RedJob to_grad_job(const float* part, int ld, int chunk0, int nchunk, int N, voi
 
 // Block x of the launch belongs to the job whose block range holds it; inside
 // the job, the block's column group and (per sample) its sample follow the
-// grids of reduce_per_sample_k and reduce_to_grad_k, and so do the sums.
+// grid of one job alone, and so do the sums.
 __global__ __launch_bounds__(1024) void reduce_jobs_k(RedJobs js) {
   __shared__ float sh[RC_SL][RC_COLS + 1];
   int k = 0;
