@@ -1285,35 +1285,58 @@ static int mfma_kind(const GemmArgs& g) {
 
 // Kernel of a forward group.  Times in units of a round of 256 x 256 tiles
 // (register-staged, one workgroup per CU), fitted to the same sweep:
+//   256 x 192 register-staged tiles, eight waves: 0.75 / 0.92 (9216 rows x
+//     9216, K 3072: 1296 large tiles 486 us, 1728 of these 471; 3072 x 12288:
+//     576 large ones 233, 768 of these 202; 9216 x 3072: 432 and 576, 162 and 184);
+//   192 x 192, four waves: 0.5625 / 0.78 (3072 rows x 3072, K 15360: 144 large
+//     tiles 305 us, 256 of these 237; K 3072 70.8 and 56.9; 4608 rows x 3072:
+//     216 and 400, 81 and 102);
 //   128 x 128 register-staged tiles, two workgroups per CU: 0.49 for up to 256
 //     tiles, 0.62 for up to 512 (2142 + 462 rows x 1536, K 1536: 66 large
 //     tiles 36.5 us, 252 small ones 17.8; 8192 + 1024 x 3072, K 3072: 432 large
-//     tiles 162 us, 1728 small ones 186);
+//     tiles 162 us, 1728 small ones 186); the second workgroup of a CU gains
+//     less over a long contraction: 0.74 from K 6144 on (1536 rows x 3072: 288
+//     of these and 144 of 192 x 192 take 44.8 and 43.7 us at K 3072, 160 and 142
+//     at K 12288);
 //   64 x 64 direct-to-LDS tiles: 0.21 per 256 (300 + 100 rows x 2304, K 768:
-//     5.7 us against 10.2 and 22.5).
+//     5.7 us against 10.2 and 22.5), 0.25 for many with K 4096 and more (1536 rows
+//     x 1024: 384 of these 34.1 us, 96 of 128 x 128 30.4).
+// The GELU epilogue (two outputs) is a larger share of a short contraction, and
+// two workgroups per CU hide one's under the other's products: 128 x 128 tiles
+// count 0.8 up to K 1024 and 0.9 up to K 2048 (8192 + 1024 rows x 4096, K 1024:
+// 140 us on large tiles, 113 on small ones; x 8192, K 2048 339 and 440; 4096 +
+// 512 rows: 180 and 167).
 // The register-staged kernels take K in whole 64-deep tiles; else the
 // direct-to-LDS ones (128 x 128: 0.55 and 0.75).
-enum { FWD_PIPE256 = DTL_64K2 + 1, FWD_PIPE128 };
+enum { FWD_PIPE256 = DTL_64K2 + 1, FWD_PIPE256x192, FWD_PIPE192, FWD_PIPE128 };
 static int fwd_shape(const GemmGroup& g, int ek) {
-  long t256 = 0, t128 = 0, t64 = 0;
+  long t256 = 0, t256x192 = 0, t192 = 0, t128 = 0, t64 = 0;
   bool k64 = true;
   for (int p = 0; p < g.np; ++p) {
     t256 += tiles_of(g.p[p], 256, 256);
+    t256x192 += tiles_of(g.p[p], 256, 192);
+    t192 += tiles_of(g.p[p], 192, 192);
     t128 += tiles_of(g.p[p], 128, 128);
     t64 += tiles_of(g.p[p], 64, 64);
     k64 = k64 && g.p[p].K % 64 == 0;
   }
-  const double one = k64 ? 0.49 : 0.55, two = k64 ? 0.62 : 0.75;
+  const int K = g.p[0].K;
+  const double one = k64 ? 0.49 : 0.55, two = !k64 ? 0.75 : K >= 6144 ? 0.74 : 0.62;
+  const double gelu = ek == EK_BIAS ? 1.0 : K <= 1024 ? 0.8 : K <= 2048 ? 0.9 : 1.0;
   const long rem = t128 % 512;
-  const double c256 = k64 ? (double)((t256 + 255) / 256) : 1e300;
-  double c128 = (double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two);
-  // the smaller tile pays more for the GELU epilogue: 3072 rows x 12288, K 3072
-  // 260 us on 256 x 256 and 288 on 128 x 128 tiles, 232 and 230 without it
-  if (ek != EK_BIAS) c128 *= 1.1;
-  const double c64 = 0.21 * (double)((t64 + 255) / 256);
-  if (c64 < c128 && c64 < c256) return dtl64(g);
-  if (c128 < c256) return k64 ? FWD_PIPE128 : DTL_128;
-  return FWD_PIPE256;
+  int best = FWD_PIPE256;
+  double bt = k64 ? (double)((t256 + 255) / 256) : 1e300;
+  auto offer = [&](int shape, double t) {
+    if (t < bt) { bt = t; best = shape; }
+  };
+  if (k64) {
+    offer(FWD_PIPE256x192, 0.75 / 0.92 * (double)((t256x192 + 255) / 256));
+    offer(FWD_PIPE192, 0.5625 / 0.78 * (double)((t192 + 255) / 256));
+  }
+  offer(k64 ? FWD_PIPE128 : DTL_128,
+        ((double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two)) * gelu);
+  offer(DTL_64, (K >= 4096 && t64 > 300 ? 0.25 : 0.21) * (double)((t64 + 255) / 256));
+  return best == DTL_64 ? dtl64(g) : best;
 }
 
 // The products of a group (all dtl_fits) in one launch.
@@ -1321,6 +1344,8 @@ template <bool TA, bool TB, int EK>
 static int run_group(const GemmGroup& g, hipStream_t s, int shape) {
   if constexpr (!TB) {
     if (shape == FWD_PIPE256) return launch_pipe<256, 256, 64, 2, 4, TA, TB, EK>(g, s);
+    if (shape == FWD_PIPE256x192) return launch_pipe<256, 192, 64, 4, 2, TA, TB, EK>(g, s);
+    if (shape == FWD_PIPE192) return launch_pipe<192, 192, 64, 2, 2, TA, TB, EK>(g, s);
     if (shape == FWD_PIPE128) return launch_pipe<128, 128, 64, 2, 2, TA, TB, EK>(g, s);
   }
   return run_dtl<TA, TB, EK>(g, s, shape);
