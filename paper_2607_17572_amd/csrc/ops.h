@@ -133,7 +133,6 @@ struct RedJob {
   void* g = nullptr;          // gradient: g[c] = beta*g[c] + sum
   int g_dt = 0;
   float beta = 0.f;
-  int blk0 = 0;               // first block of the job (set by reduce_jobs)
 };
 constexpr int RED_MAX_JOBS = 24;  // a double block's
 RedJob per_sample_job(const float* part, int N, RowMap rm, int row0, int nrows, float* out, int out_stride,

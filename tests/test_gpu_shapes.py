@@ -92,6 +92,19 @@ def test_bf16_products_of_a_pass(c, B):
     check_pass(c, B, 3, 2e-2)
 
 
+# forward products on 192 x 192 and 256 x 192 tiles, ragged in both streams' rows: the MLP's first layer of a double
+# block and a single block's whole input projection (24192-wide MLP: 252 and 254 tiles in one round of the CUs), and a
+# q/k/v projection (252 tiles of 192 x 192; 204 of 256 x 192)
+@pytest.mark.parametrize("c,B", [
+    (block(1, 64, 75, 38, 10, act=pk.BF16, mlp_hidden=24192, block_only=0, n_single=1), 1),
+    (block(1, 64, 100, 50, 10, act=pk.BF16, mlp_hidden=24192, block_only=0, n_single=1), 1),
+    (block(3, 128, 40, 58, 66, act=pk.BF16, mlp_hidden=64), 4),
+    (block(3, 128, 43, 62, 66, act=pk.BF16, mlp_hidden=64), 4),
+], ids=["mlp192", "mlp256x192", "qkv192", "qkv256x192"])
+def test_bf16_forward_tiles(c, B):
+    check_pass(c, B, 2, 2e-2)
+
+
 # time MLP and modulations at each samples-per-thread form of their backward (batch 2, 4, 8, 16, 32 of the pair), rows
 # that are not a multiple of the 8-row tiles, and a frequency width without 16-byte rows
 @pytest.mark.parametrize("B,over", [(1, {}), (2, {}), (3, {}), (6, {}), (13, {}), (2, dict(t_freq_dim=250))],
