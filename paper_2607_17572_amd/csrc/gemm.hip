@@ -1216,8 +1216,9 @@ static int run_dtl(const GemmGroup& g, hipStream_t s, int shape) {
 }
 
 // The direct-to-LDS kernel computes 32-bit byte offsets up to six k tiles past
-// K (three of prefetch, three of a k group without tiles); they must stay below 2^31.  A ragged last k tile needs both operands
-// k-strided: their rows past K lie past the operands' ends and read as zeros.
+// K (three of prefetch, three of a k group without tiles); they must stay below
+// 2^31.  A ragged last k tile needs both operands k-strided: their rows past K
+// lie past the operands' ends and read as zeros.
 static bool dtl_fits(const GemmArgs& g) {
   const double kx = (double)g.K + 224.0;
   const double ea = 2.0 * (g.ta ? kx * g.lda + g.M : (double)g.M * g.lda + kx);
