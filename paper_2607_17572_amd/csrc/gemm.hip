@@ -1175,10 +1175,10 @@ static int dtl64(const GemmGroup& g) {
 // sweep of twelve row counts x four layers x both products: the choice is
 // within 8% of the best shape on all of them.  Examples (us; 256x192, 192x192,
 // 128x128, 64x64): 2048 + 616 rows x 768, K 3072: 49 / 42 / 30 / 27; 2142 + 462
-// x 1536, K 6144: 89 / 76 / 58 / 102; 8192 + 1024 x 12288, K 3072: 633 / 652 /
+// x 1536, K 6144: 89 / 76 / 58 / 102; 3072 x 1536, K 6144: - / 78 / 99 / 106; 8192 + 1024 x 12288, K 3072: 633 / 652 /
 // 912 / 1242 (256x256: 562).
 static int dtl_shape(const GemmGroup& g) {
-  static const double eff[DTL_SHAPES] = {1.0, 0.95, 0.95, 0.8, 0.7, 0.5};
+  static const double eff[DTL_SHAPES] = {1.0, 0.95, 0.95, 0.8, 0.7, 0.4};
   int best = 0;
   double bt = 1e300;
   for (int i = 0; i < DTL_SHAPES; ++i) {
@@ -1296,12 +1296,13 @@ static int mfma_kind(const GemmArgs& g) {
 //     tiles, 0.62 for up to 512 (2142 + 462 rows x 1536, K 1536: 66 large
 //     tiles 36.5 us, 252 small ones 17.8; 8192 + 1024 x 3072, K 3072: 432 large
 //     tiles 162 us, 1728 small ones 186); the second workgroup of a CU gains
-//     less over a long contraction: 0.74 from K 6144 on (1536 rows x 3072: 288
+//     less over a long contraction: 0.74 from K 4608 on (1536 rows x 3072: 288
 //     of these and 144 of 192 x 192 take 44.8 and 43.7 us at K 3072, 160 and 142
 //     at K 12288);
 //   64 x 64 direct-to-LDS tiles: 0.21 per 256 (300 + 100 rows x 2304, K 768:
-//     5.7 us against 10.2 and 22.5), 0.25 for many with K 4096 and more (1536 rows
-//     x 1024: 384 of these 34.1 us, 96 of 128 x 128 30.4).
+//     5.7 us against 10.2 and 22.5), 0.25 for many with K 3072 and more (1536 rows
+//     x 1024, K 4096: 384 of these 34.1 us, 96 of 128 x 128 30.4; 2604 x 768, K
+//     3072: 504 and 126, 27.7 and 25.2).
 // The GELU epilogue (two outputs) is a larger share of a short contraction, and
 // two workgroups per CU hide one's under the other's products: 128 x 128 tiles
 // count 0.8 up to K 1024 and 0.9 up to K 2048 (8192 + 1024 rows x 4096, K 1024:
@@ -1322,7 +1323,7 @@ static int fwd_shape(const GemmGroup& g, int ek) {
     k64 = k64 && g.p[p].K % 64 == 0;
   }
   const int K = g.p[0].K;
-  const double one = k64 ? 0.49 : 0.55, two = !k64 ? 0.75 : K >= 6144 ? 0.74 : 0.62;
+  const double one = k64 ? 0.49 : 0.55, two = !k64 ? 0.75 : K >= 4608 ? 0.74 : 0.62;
   const double gelu = ek == EK_BIAS ? 1.0 : K <= 1024 ? 0.8 : K <= 2048 ? 0.9 : 1.0;
   const long rem = t128 % 512;
   int best = FWD_PIPE256;
@@ -1336,7 +1337,7 @@ static int fwd_shape(const GemmGroup& g, int ek) {
   }
   offer(k64 ? FWD_PIPE128 : DTL_128,
         ((double)(t128 / 512) * two + (rem == 0 ? 0.0 : rem <= 256 ? one : two)) * gelu);
-  offer(DTL_64, (K >= 4096 && t64 > 300 ? 0.25 : 0.21) * (double)((t64 + 255) / 256));
+  offer(DTL_64, (K >= 3072 && t64 > 300 ? 0.25 : 0.21) * (double)((t64 + 255) / 256));
   return best == DTL_64 ? dtl64(g) : best;
 }
 
