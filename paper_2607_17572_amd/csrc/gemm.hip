@@ -1175,8 +1175,8 @@ static int dtl64(const GemmGroup& g) {
 // sweep of twelve row counts x four layers x both products: the choice is
 // within 8% of the best shape on all of them.  Examples (us; 256x192, 192x192,
 // 128x128, 64x64): 2048 + 616 rows x 768, K 3072: 49 / 42 / 30 / 27; 2142 + 462
-// x 1536, K 6144: 89 / 76 / 58 / 102; 3072 x 1536, K 6144: - / 78 / 99 / 106; 8192 + 1024 x 12288, K 3072: 633 / 652 /
-// 912 / 1242 (256x256: 562).
+// x 1536, K 6144: 89 / 76 / 58 / 102; 3072 x 1536, K 6144: - / 78 / 99 / 106;
+// 8192 + 1024 x 12288, K 3072: 633 / 652 / 912 / 1242 (256x256: 562).
 static int dtl_shape(const GemmGroup& g) {
   static const double eff[DTL_SHAPES] = {1.0, 0.95, 0.95, 0.8, 0.7, 0.4};
   int best = 0;
