@@ -302,9 +302,15 @@ static int sl_parts(int cpt, int Din, int Dout, int np) {
   return (Dout + jt - 1) / jt;
 }
 
+// Never less than for a smaller batch, so that a workspace serves those too: the
+// parts shrink where the columns per thread do (batch 5 and 9), and between
+// these the size grows with the batch.
 size_t small_linear_bwd_part_floats(int B, int Din, int Dout, int np) {
-  // rows that are not aligned for the vector kernel take one column per thread
-  return (size_t)np * std::max(sl_parts(sl_cpt(B), Din, Dout, np), sl_parts(1, Din, Dout, np)) * B * Din;
+  size_t most = 0;
+  for (const int b : {std::min(B, 4), std::min(B, 8), B})
+    // rows that are not aligned for the vector kernel take one column per thread
+    most = std::max(most, (size_t)np * std::max(sl_parts(sl_cpt(b), Din, Dout, np), sl_parts(1, Din, Dout, np)) * b * Din);
+  return most;
 }
 
 // out[i] (+)= sum over p of part[p * n + i], parts added in a fixed order: 64

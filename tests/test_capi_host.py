@@ -2,6 +2,7 @@
 every function declared in include/jagg.h, its parameter layout equals the
 oracle's, and the host-only routing and interpolation-weight calls agree with
 the oracle bit for bit."""
+import ctypes
 import json
 import os
 import re
@@ -288,4 +289,28 @@ def test_trajectory_and_quality_reject_bad_arguments():
         assert L.jagg_window_quality(h, p, p, st4, 1, st4, t4b, 4, p, p, p, out) == 1  # t not decreasing
         assert L.jagg_window_quality(h, p, None, st4, 1, st4, t4, 4, p, p, p, out) == 1
     finally:
+        L.jagg_ctx_destroy(h)
+
+
+# A context sized for a batch runs every smaller one (a window after a larger one, the per-step part of a trajectory
+# beside its windows of twice the batch), so neither buffer may shrink as the batch grows.  Few tokens and wide hidden
+# sizes: the modulations' partial sums, whose split depends on the batch, are a large share of the workspace.
+@pytest.mark.parametrize("heads,head_dim", [(4, 16), (12, 64), (8, 128), (12, 128), (16, 128), (24, 128), (32, 128)])
+@pytest.mark.parametrize("n_txt,lat", [(4, 4), (16, 8)])
+@pytest.mark.parametrize("block_only", [0, 1])
+def test_buffer_sizes_grow_with_the_batch(heads, head_dim, n_txt, lat, block_only):
+    L = _lib_or_skip()
+    d = heads * head_dim
+    for act in (pk.F32, pk.BF16):
+        c = pk.Config(n_double=1, n_single=0 if block_only else 1, hidden=d, heads=heads, head_dim=head_dim,
+                      mlp_hidden=4 * d, in_ch=16, patch=2, lat_h=lat, lat_w=lat, n_txt=n_txt, txt_dim=64,
+                      t_freq_dim=256, block_only=block_only, act_dtype=act).c()
+        h, n = ctypes.c_void_p(), ctypes.c_size_t()
+        assert L.jagg_ctx_create(ctypes.byref(c), None, ctypes.byref(h)) == 0
+        for f in (L.dit_workspace_bytes, L.dit_saved_bytes):
+            sizes = []
+            for b in range(1, 33):
+                assert f(h, b, ctypes.byref(n)) == 0
+                sizes.append(n.value)
+            assert sizes == sorted(sizes), (f.__name__, act, sizes)
         L.jagg_ctx_destroy(h)
