@@ -1202,49 +1202,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // LDS reads in the same contraction-slot order; dQ^T += K^T dS^T.  No scores
 // are recomputed: the pass is bound by reading dS^T once.  Eight waves, two
 // per SIMD: wave w takes query block w % 4 (32 queries) and head-dimension
-// half w / 4 (32-row blocks of dQ^T: two at D = 128, one at 64), so a wave that waits to issue its
+// half w / 4 (two 32-row blocks of dQ^T), so a wave that waits to issue its
 // direct loads leaves the SIMD to the other wave's fragment reads and MFMAs.
 // The 1 KB loads of each tile are dealt evenly to the waves.
 constexpr int Q4_QB = 128, Q4_KT = 64;
 
-template <int D>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_q4_k(AttnBwd a) {
-  typedef AGeo<D> G;
-  typedef AGeo<128> GS;              // a dS^T tile row is 128 queries
-  constexpr int KL = G::TILE / 8192; // K slots per wave and tile
+  typedef AGeo<DH> G;                // of K and dS^T alike: a dS^T tile row is 128 queries
+  constexpr int KL = G::TILE / 8192; // slots per wave, tile and operand
   constexpr int ND = G::DT / 2;      // 32-row blocks of dQ^T per wave
-  __shared__ __attribute__((aligned(1024))) char K0[G::TILE], S0[16384], K1[G::TILE], S1[16384], K2[G::TILE], S2[16384],
-      K3[G::TILE], S3[16384];
+  __shared__ __attribute__((aligned(1024))) char K0[G::TILE], S0[G::TILE], K1[G::TILE], S1[G::TILE], K2[G::TILE], S2[G::TILE],
+      K3[G::TILE], S3[G::TILE];
   const int bh = blockIdx.y;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, c32 = lane & 31;
   const int qw = w & 3, dh = w >> 2;
   const int qb = blockIdx.x * Q4_QB;
   const int q = qb + qw * 32 + c32;
   const int N = a.N;
-  const size_t base = (size_t)bh * N * D;
-  const float sc = rsqrtf((float)D);
+  const size_t base = (size_t)bh * N * DH;
+  const float sc = rsqrtf((float)DH);
   const __amdgpu_buffer_rsrc_t RK = arsrc((const uint16_t*)a.K + base, (long)N * G::ROWB);
   const __amdgpu_buffer_rsrc_t RS =
       arsrc((const uint16_t*)a.dS + (size_t)bh * a.nk_pad * a.ld_ds, (long)a.nk_pad * a.ld_ds * 2);
-  // direct-load slots of this wave: KL of K, 2 of dS^T;
+  // direct-load slots of this wave, KL of K and of dS^T;
   // sof[t]: the slot's byte offset in a tile of the chunked dS^T (a tile row
   // is 128 queries: source chunks 0-7 in the chunk of the block's first 64
   // queries, 8-15 in the next chunk, 16 KB on)
   // kof[t]: the slot's byte offset in a K tile at k0 = 0
-  int sof[2], kof[KL];
+  int sof[KL], kof[KL];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int lch = GS::slot_chunk(2 * w + t, lane);
-    sof[t] = GS::slot_row(2 * w + t, lane) * 128 + (lch >> 3) * 16384 + (lch & 7) * 16;
+  for (int t = 0; t < KL; ++t) {
+    const int lrow = G::slot_row(KL * w + t, lane), lch = G::slot_chunk(KL * w + t, lane);
+    sof[t] = lrow * 128 + (lch >> 3) * 16384 + (lch & 7) * 16;
+    kof[t] = lrow * G::ROWB + lch * 16;
   }
-#pragma unroll
-  for (int t = 0; t < KL; ++t)
-    kof[t] = G::slot_row(KL * w + t, lane) * G::ROWB + G::slot_chunk(KL * w + t, lane) * 16;
   const int nqt = a.ld_ds / 64;
   // Offsets of the transposing reads, for blocks known only at run time:
   // computed rather than indexed, so that they stay in registers (a dynamic
   // index moves the arrays to LDS and costs a strided LDS read per use)
-  const int2 wsel = GS::tr_off(lane, qw);
+  const int2 wsel = G::tr_off(lane, qw);
   int2 dsel[ND];
   f32x16 dq[ND];
 #pragma unroll
@@ -1262,8 +1258,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int t = 0; t < KL; ++t)
       lds_load<16>(RK, Kd + (KL * wave + t) * 1024, kpart + kof[t]);
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-      lds_load<16>(RS, Sd + (2 * wave + t) * 1024, spart + sof[t]);
+    for (int t = 0; t < KL; ++t)
+      lds_load<16>(RS, Sd + (KL * wave + t) * 1024, spart + sof[t]);
   };
   // Every tile load is issued whether the tile exists or not, so that the
   // issue order (and the waits the compiler derives from it) is the same in
@@ -1280,8 +1276,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     char* Sc = c == 0 ? S0 : (c == 1 ? S1 : (c == 2 ? S2 : S3));
     const int k0 = it * Q4_KT;
     // tile it has landed once at most the loads of the two later tiles in
-    // flight (KL + 2 direct loads per tile and wave) are outstanding
-    attn_barrier<2 * (KL + 2)>();
+    // flight (2 KL direct loads per tile and wave) are outstanding
+    attn_barrier<4 * KL>();
     // the stage of tile it+3 was last read in iteration it-1
     if constexpr (c == 0) load_tile(K3, S3, k0 + 3 * Q4_KT);
     else if constexpr (c == 1) load_tile(K0, S0, k0 + 3 * Q4_KT);
@@ -1291,7 +1287,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto frags = [&](int cb, int buf) {
 #pragma unroll
       for (int j = 0; j < ND; ++j) tk[buf][j] = tr_pair(Kc + cb * 16 * G::ROWB, dsel[j].x, dsel[j].y);
-      ts[buf] = tr_pair(Sc + cb * 16 * GS::ROWB, wsel.x, wsel.y);
+      ts[buf] = tr_pair(Sc + cb * 16 * G::ROWB, wsel.x, wsel.y);
     };
     frags(0, 0);
 #pragma unroll
@@ -1316,7 +1312,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       bf16x4 v;
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = (__bf16)(dq[j][4 * g + i] * sc);
-      *(bf16x4*)((uint16_t*)a.dQ + base + (size_t)q * D + 32 * (ND * dh + j) + 8 * g + 4 * h) = v;
+      *(bf16x4*)((uint16_t*)a.dQ + base + (size_t)q * DH + 32 * (ND * dh + j) + 8 * g + 4 * h) = v;
     }
 }
 
@@ -1345,19 +1341,27 @@ int attention_fwd_mfma(const AttnFwd& a, hipStream_t s) {
   return 0;
 }
 
-// The direct-load backward: dS^T stored when it fits (ds), else recomputed.
+// The direct-load backward.  Head dim 128: dS^T stored when it fits (ds), else
+// recomputed.  Head dim 64 always recomputes it: dS^T is B H N^2 elements, at 64
+// twice as many per hidden size, and the two score products cost half as much
+// (a step of 8 samples of 333 tokens x 12 heads takes 498 us, with it stored 500).
 template <int D>
 static int bwd_direct(const AttnBwd& a, bool ds, hipStream_t s) {
   const double nn = (double)a.B * a.H * a.N * (double)a.N * D;
-  const dim3 gkv((a.N + KV5_KB - 1) / KV5_KB, a.B * a.H), gq((a.N + Q4_QB - 1) / Q4_QB, a.B * a.H);
+  const dim3 gkv((a.N + KV5_KB - 1) / KV5_KB, a.B * a.H), gq((a.N + Q2_QB - 1) / Q2_QB, a.B * a.H);
+  static_assert(Q2_QB == Q4_QB, "one grid for both dQ kernels");
   int pi = prof_begin(PROF_ATTN_BWD_KV);
-  if (ds) launch(attn_bwd_kv5_k<D, true>, gkv, dim3(512), 0u, s, a);
-  else launch(attn_bwd_kv5_k<D, false>, gkv, dim3(512), 0u, s, a);
+  if constexpr (D == 128) {
+    if (ds) launch(attn_bwd_kv5_k<D, true>, gkv, dim3(512), 0u, s, a);
+    else launch(attn_bwd_kv5_k<D, false>, gkv, dim3(512), 0u, s, a);
+  } else {
+    launch(attn_bwd_kv5_k<D, false>, gkv, dim3(512), 0u, s, a);
+  }
   prof_end(pi, 6.0 * nn);
   JG_CHECK_LAUNCH("attention_bwd_kv_mfma");
   pi = prof_begin(PROF_ATTN_BWD_Q);
-  if (ds) launch(attn_bwd_q4_k<D>, gq, dim3(512), 0u, s, a);
-  else launch(attn_bwd_q2_k<D>, dim3((a.N + Q2_QB - 1) / Q2_QB, a.B * a.H), dim3(256), 0u, s, a);
+  if (D == 128 && ds) launch(attn_bwd_q4_k, gq, dim3(512), 0u, s, a);
+  else launch(attn_bwd_q2_k<D>, gq, dim3(256), 0u, s, a);
   prof_end(pi, 2.0 * nn);
   JG_CHECK_LAUNCH("attention_bwd_q_mfma");
   return 0;

@@ -297,7 +297,7 @@ static size_t plan_ws(const Model& m, int B, void* base, Ws& W) {
   W.dKh = a.take(hn * m.Dh * es);
   W.dVh = a.take(hn * m.Dh * es);
   W.delta = a.f32(2 * hn);  // delta, then the log-sum-exp in log2 units
-  if (m.act == BF16 && (m.Dh == 128 || m.Dh == 64))
+  if (m.act == BF16 && m.Dh == 128)
     W.dS = a.take((size_t)B * m.H * attn_ds_rows(m.N) * attn_ds_ld(m.N) * 2);
   // per 32-row chunk: the widest partials of one launch (the LayerNorm
   // backward's come per block of LN_ROWS rows, RED_ROWS / LN_ROWS per chunk)

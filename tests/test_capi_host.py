@@ -314,3 +314,21 @@ def test_buffer_sizes_grow_with_the_batch(heads, head_dim, n_txt, lat, block_onl
                 sizes.append(n.value)
             assert sizes == sorted(sizes), (f.__name__, act, sizes)
         L.jagg_ctx_destroy(h)
+
+
+# Only the bf16 attention backward with head dim 128 stores dS^T (tokens x tokens per head); every other workspace is
+# linear in the tokens (4 x the image tokens and text tokens: 4 x the bytes, and less for the parts without tokens).
+@pytest.mark.parametrize("act,head_dim", [(pk.BF16, 64), (pk.BF16, 32), (pk.BF16, 16), (pk.F32, 128), (pk.F32, 64)])
+def test_workspace_is_linear_in_the_tokens(act, head_dim):
+    L = _lib_or_skip()
+    size = []
+    for k in (1, 2):
+        c = pk.Config(n_double=1, n_single=0, hidden=12 * head_dim, heads=12, head_dim=head_dim,
+                      mlp_hidden=48 * head_dim, in_ch=16, patch=2, lat_h=64 * k, lat_w=64 * k, n_txt=256 * k * k,
+                      txt_dim=64, t_freq_dim=256, block_only=1, act_dtype=act).c()
+        h, n = ctypes.c_void_p(), ctypes.c_size_t()
+        assert L.jagg_ctx_create(ctypes.byref(c), None, ctypes.byref(h)) == 0
+        assert L.dit_workspace_bytes(h, 2, ctypes.byref(n)) == 0
+        size.append(n.value)
+        L.jagg_ctx_destroy(h)
+    assert size[1] <= 4.01 * size[0], size
