@@ -1,5 +1,6 @@
 // Flash attention forward and backward on gfx950 MFMA (bf16 in, fp32
-// accumulation), head dim 128 and 64 (D in the templates below).
+// accumulation), head dim 128 and 64 (D in the templates below).  At 128 the
+// probabilities and dS enter their products as bf16, at 64 as two bf16 parts.
 //
 // Layout trick: every score tile is computed in the orientation whose MFMA
 // accumulator can feed the next MFMA directly as its "B" operand.  With
@@ -61,6 +62,15 @@ __device__ inline bf16x8 pack8(const f32x16& v, int c) {
   bf16x8 r;
 #pragma unroll
   for (int i = 0; i < 8; ++i) r[i] = (__bf16)v[8 * c + i];
+  return r;
+}
+
+// the rest of those values after pack8, as a second fragment: the two together
+// carry 17 bits of each value
+__device__ inline bf16x8 pack8_rest(const f32x16& v, int c, bf16x8 hi) {
+  bf16x8 r;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = (__bf16)(v[8 * c + i] - (float)hi[i]);
   return r;
 }
 
@@ -599,6 +609,12 @@ struct AGeo {
   static constexpr int KB = D / 16, DT = D / 32;   // 16-deep steps and 32-column blocks
   static constexpr int SR = 1024 / ROWB;           // rows of a 1 KB direct load (slot)
   static constexpr int TILE = 64 * ROWB;           // bytes of a 64-row tile
+  // P and dS enter their products as two bf16 fragments (pack8, pack8_rest):
+  // head dim 64 keeps the precision of fp32 probabilities, its results are the
+  // fp64 ones rounded once (relative error of O 1.66e-3; 2.3e-3 with one
+  // fragment).  Forward and backward of 2 samples of 4608 tokens x 24 heads:
+  // 413 and 1375 us; with one, and dS^T stored for the dQ pass, 322 and 1450.
+  static constexpr bool SPLIT = D == 64;
   // tile row and source chunk that this lane loads for slot s
   static __device__ inline int slot_row(int s, int lane) { return SR * s + lane / CH; }
   static __device__ inline int slot_chunk(int s, int lane) { return (lane % CH) ^ asw<D>(slot_row(s, lane)); }
@@ -850,8 +866,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
       }
 #pragma unroll
       for (int dt = 0; dt < G::DT; ++dt) {
-        dv[dt] = mfma(trf(blk, dt, GOF), pb, dv[dt]);
-        dk[dt] = mfma(trf(blk, dt, 0), db, dk[dt]);
+        const bf16x8 tg = trf(blk, dt, GOF), tq = trf(blk, dt, 0);
+        dv[dt] = mfma(tg, pb, dv[dt]);
+        dk[dt] = mfma(tq, db, dk[dt]);
+        if constexpr (G::SPLIT) {
+          dv[dt] = mfma(tg, pack8_rest(st, blk, pb), dv[dt]);
+          dk[dt] = mfma(tq, pack8_rest(dpt, blk, db), dk[dt]);
+        }
       }
     }
   };
@@ -1027,6 +1048,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
       for (int dt = 0; dt < G::DT; ++dt) tv[dt] = at.tr(Vc, cb, dt);
 #pragma unroll
       for (int dt = 0; dt < G::DT; ++dt) o[dt] = mfma(tv[dt], pb, o[dt]);
+      if constexpr (G::SPLIT) {
+        const bf16x8 pr = pack8_rest(st[cb >> 1], cb & 1, pb);
+#pragma unroll
+        for (int dt = 0; dt < G::DT; ++dt) o[dt] = mfma(tv[dt], pr, o[dt]);
+      }
     }
   };
   using F = std::false_type;
@@ -1159,6 +1185,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const bf16x8 db = pack8(dpt, half);
 #pragma unroll
         for (int dt = 0; dt < G::DT; ++dt) dq[dt] = mfma(tk[half][dt], db, dq[dt]);
+        if constexpr (G::SPLIT) {
+          const bf16x8 dr = pack8_rest(dpt, half, db);
+#pragma unroll
+          for (int dt = 0; dt < G::DT; ++dt) dq[dt] = mfma(tk[half][dt], dr, dq[dt]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1323,7 +1354,7 @@ static bool mfma_ok(int Dh, int dt, const void* O, int ld_o) {
 
 // Head dim 64: on the vector ALUs (one score at a time per four lanes) the
 // three passes took 134, 167 and 259 us for 8 samples of 333 tokens x 12
-// heads; here 13, 37 and 13.  The register-staged kernels for offsets beyond 32 bits
+// heads; here 17, 26 and 23.  The register-staged kernels for offsets beyond 32 bits
 // exist for 128 only.
 int attention_fwd_mfma(const AttnFwd& a, hipStream_t s) {
   if (!mfma_ok(a.Dh, a.dt, a.O, a.ld_o)) return -1;
