@@ -62,6 +62,16 @@ struct Row {
 #pragma unroll
     for (int kb = 0; kb < D / 8; ++kb) ld4(row + 8 * kb + 4 * h, f + 4 * kb);
   }
+  // of a token-major operand; VEC: its rows allow the four-element loads
+  template <bool VEC>
+  __device__ inline void load_tok(const T* row, int h) {
+    if constexpr (VEC) {
+      load(row, h);
+    } else {
+#pragma unroll
+      for (int i = 0; i < D / 2; ++i) f[i] = ldf(row, 8 * (i >> 2) + 4 * h + (i & 3));
+    }
+  }
 };
 template <int D, typename T>
 __device__ inline f32x16 score(const Row<D, T>& a, const Row<D, T>& b) {
@@ -181,7 +191,7 @@ __device__ inline float row_dot(const Row<D, T>& a, const Row<D, T>& b) {
 
 // The row sums delta = sum_d dO O are formed where they are needed (per query
 // of a tile, per column), from a row of O beside the row of dO.
-template <int D, typename T>
+template <int D, typename T, bool VEC>
 __device__ __forceinline__ void bwd_kv_f32(const AttnBwd& a, float* part) {
   constexpr int DT = (D + 31) / 32;
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H, N = a.N;
@@ -204,10 +214,10 @@ __device__ __forceinline__ void bwd_kv_f32(const AttnBwd& a, float* part) {
     Row<D, T> x;
     x.load(qrow(c32), h);
     f32x16 p = score<D, T>(x, kr);
-    x.load(grow(c32), h);
+    x.template load_tok<VEC>(grow(c32), h);
     f32x16 ds = score<D, T>(x, vr);
     Row<D, T> o;
-    o.load((const T*)a.O + (size_t)row_of_tok(a.rm, b, min(q0 + c32, N - 1)) * a.ld_o + hd * D, h);
+    o.template load_tok<VEC>((const T*)a.O + (size_t)row_of_tok(a.rm, b, min(q0 + c32, N - 1)) * a.ld_o + hd * D, h);
     const float delta = row_dot<D, T>(x, o);  // of query q0 + c32
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -228,7 +238,7 @@ __device__ __forceinline__ void bwd_kv_f32(const AttnBwd& a, float* part) {
   merge<D>(part, dk, w, h, c32, put(a.dK, scale));
 }
 
-template <int D, typename T>
+template <int D, typename T, bool VEC>
 __device__ __forceinline__ void bwd_q_f32(const AttnBwd& a, float* part) {
   constexpr int DT = (D + 31) / 32;
   const int bh = blockIdx.y, b = bh / a.H, hd = bh % a.H, N = a.N;
@@ -239,9 +249,9 @@ __device__ __forceinline__ void bwd_q_f32(const AttnBwd& a, float* part) {
   const float scale = rsqrtf((float)D), sc = scale * LOG2E_F;
   Row<D, T> qr, gr;
   qr.load(Q + (size_t)qc * D, h);
-  gr.load((const T*)a.dO + (size_t)row_of_tok(a.rm, b, qc) * a.ld_do + hd * D, h);
+  gr.template load_tok<VEC>((const T*)a.dO + (size_t)row_of_tok(a.rm, b, qc) * a.ld_do + hd * D, h);
   Row<D, T> o;
-  o.load((const T*)a.O + (size_t)row_of_tok(a.rm, b, qc) * a.ld_o + hd * D, h);
+  o.template load_tok<VEC>((const T*)a.O + (size_t)row_of_tok(a.rm, b, qc) * a.ld_o + hd * D, h);
   const float l2 = a.lse[(size_t)bh * N + qc] * LOG2E_F, dl = row_dot<D, T>(gr, o);
   f32x16 dq[DT];
 #pragma unroll
@@ -264,11 +274,11 @@ __device__ __forceinline__ void bwd_q_f32(const AttnBwd& a, float* part) {
 
 // Both passes in one launch (z = 0: dK and dV, 1: dQ): they are independent,
 // and at few tokens neither fills the chip.
-template <int D, typename T>
+template <int D, typename T, bool VEC>
 __global__ __launch_bounds__(256) void attn_bwd_f32_k(AttnBwd a) {
   __shared__ float part[4 * D * 33];
-  if (blockIdx.z == 0) bwd_kv_f32<D, T>(a, part);
-  else bwd_q_f32<D, T>(a, part);
+  if (blockIdx.z == 0) bwd_kv_f32<D, T, VEC>(a, part);
+  else bwd_q_f32<D, T, VEC>(a, part);
 }
 
 // ------------------------------------------------------------------ launch
@@ -277,8 +287,10 @@ static void fwd_f32(const AttnFwd& a, hipStream_t s) {
   hipLaunchKernelGGL((attn_fwd_f32_k<D, T>), dim3((a.N + 31) / 32, a.B * a.H), dim3(256), 0, s, a);
 }
 template <int D, typename T>
-static void bwd_f32(const AttnBwd& a, hipStream_t s) {
-  hipLaunchKernelGGL((attn_bwd_f32_k<D, T>), dim3((a.N + 31) / 32, a.B * a.H, 2), dim3(256), 0, s, a);
+static void bwd_f32(const AttnBwd& a, bool vec, hipStream_t s) {
+  const dim3 grid((a.N + 31) / 32, a.B * a.H, 2);
+  if (vec) hipLaunchKernelGGL((attn_bwd_f32_k<D, T, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((attn_bwd_f32_k<D, T, false>), grid, dim3(256), 0, s, a);
 }
 
 int attention_fwd_mfma(const AttnFwd& a, hipStream_t s);  // attention_mfma.hip; returns -1 if not applicable
@@ -305,12 +317,11 @@ int attention_bwd(const AttnBwd& a, hipStream_t s) {
   if (a.N <= 0 || a.B <= 0 || a.H <= 0) { set_error("attention_bwd: empty problem"); return 1; }
   const int rc = attention_bwd_mfma(a, s);
   if (rc >= 0) return rc;
-  if (a.dt_d != a.dt || !rows_ok(a.dO, a.ld_do, a.dt) || !rows_ok(a.O, a.ld_o, a.dt)) {
-    set_error("attention_bwd: gradients in another type, or unaligned rows");
-    return 4;
-  }
+  if (a.dt_d != a.dt) { set_error("attention_bwd: gradients in another type"); return 4; }
+  // (a single block's O lies in rows of hidden + mlp_hidden elements)
+  const bool vec = rows_ok(a.dO, a.ld_do, a.dt) && rows_ok(a.O, a.ld_o, a.dt);
   switch (a.Dh) {
-#define JG_DIM(D) case D: a.dt == BF16 ? bwd_f32<D, uint16_t>(a, s) : bwd_f32<D, float>(a, s); break;
+#define JG_DIM(D) case D: a.dt == BF16 ? bwd_f32<D, uint16_t>(a, vec, s) : bwd_f32<D, float>(a, vec, s); break;
     JG_DIM(16) JG_DIM(32) JG_DIM(64) JG_DIM(128)
 #undef JG_DIM
     default: set_error("attention_bwd: head_dim must be 16, 32, 64 or 128"); return 4;

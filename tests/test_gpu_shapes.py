@@ -144,3 +144,12 @@ def test_group_score_forms(n, off, dt, W):
 @pytest.mark.parametrize("act", [pk.F32, pk.BF16])
 def test_norm_widths(heads, head_dim, act):
     check_pass(block(heads, head_dim, 3, 4, 6, act=act, mlp_hidden=64), 1, 2, 2e-2 if act == pk.BF16 else 1e-4)
+
+
+# a single block whose rows of q, k, v and MLP (3 hidden + MLP) and of attention output and MLP (hidden + MLP) are not
+# multiples of four elements: products, attention and q/k norm on their element loads
+@pytest.mark.parametrize("heads,head_dim", [(4, 16), (2, 64), (1, 128)])
+@pytest.mark.parametrize("act", [pk.F32, pk.BF16])
+def test_mlp_widths_of_a_single_block(heads, head_dim, act):
+    check_pass(block(heads, head_dim, 9, 4, 6, act=act, block_only=0, n_single=1, mlp_hidden=170), 1, 2,
+               2e-2 if act == pk.BF16 else 1e-4)
