@@ -162,6 +162,7 @@ __device__ __forceinline__ u32x4 pack8(const float* f) {
 // 8 consecutive outputs of one row, all inside C (vector path)
 template <int EK>
 __device__ __forceinline__ void epi8(const Epi& e, int row, int col, float* v) {
+  static_assert(EK != EK_BIAS_GELU, "a group's kernel picks the kind of its problem");
   if (EK == EK_BIAS || EK == EK_GELU) {
     float bb[8];
     unpack8(*(const u32x4*)((const uint16_t*)e.bias + col), bb);
@@ -205,6 +206,7 @@ __device__ __forceinline__ void epi8(const Epi& e, int row, int col, float* v) {
 // one output element (edge path)
 template <int EK>
 __device__ __forceinline__ void epi1(const Epi& e, int row, int col, float v) {
+  static_assert(EK != EK_BIAS_GELU, "a group's kernel picks the kind of its problem");
   if (EK == EK_BIAS || EK == EK_GELU) v += bf2f(((const uint16_t*)e.bias)[col]);
   if (EK == EK_GELU) {
     ((uint16_t*)e.aux)[(size_t)row * e.ldaux + col] = f2bf(v);
@@ -1374,8 +1376,8 @@ static int with_kind(const GemmArgs& g, int ek, F f) {
 #undef JG_KIND
 }
 
-static int launch_group(const GemmGroup& g, int ek, hipStream_t s, int shape = -1) {
-  if (shape < 0) shape = g.p[0].tb ? dtl_shape(g) : fwd_shape(g, ek);
+static int launch_group(const GemmGroup& g, int ek, hipStream_t s) {
+  const int shape = g.p[0].tb ? dtl_shape(g) : fwd_shape(g, ek);
   return with_kind(g.p[0], ek, [&](auto ta, auto tb, auto k) {
     return run_group<decltype(ta)::value, decltype(tb)::value, decltype(k)::value>(g, s, shape);
   });
@@ -1395,7 +1397,8 @@ static int gemm_launch(const GemmArgs& g, hipStream_t s) {
   // ragged k of a k-contiguous operand (or offsets near 2^31): the
   // edge-checked kernel
   return with_kind(g, ek, [&](auto ta, auto tb, auto k) {
-    return launch_mfma<decltype(ta)::value, decltype(tb)::value, decltype(k)::value>(g, s);
+    if constexpr (decltype(k)::value == EK_BIAS_GELU) return 1;  // groups only: no single product has it
+    else return launch_mfma<decltype(ta)::value, decltype(tb)::value, decltype(k)::value>(g, s);
   });
 }
 
