@@ -643,11 +643,9 @@ int ln_mod_fwd(const void* x, int act_dt, int D, RowMap rm, int row0, int nrows,
     LAUNCH_OK("ln_mod_fwd_vec");
     return 0;
   }
-  if (copy && hipMemcpyAsync((char*)copy + (size_t)row0 * D * dsize(act_dt), (const char*)x + (size_t)row0 * D * dsize(act_dt),
-                             (size_t)nrows * D * dsize(act_dt), hipMemcpyDeviceToDevice, s) != hipSuccess) {
-    set_error("ln_mod_fwd: copy of the input rows failed");
-    return 3;
-  }
+  // hidden not a multiple of 8: only the final LayerNorm of a network without
+  // blocks, since the head dims that attention takes are multiples of 16
+  if (copy) { set_error("ln_mod_fwd: head_dim must be 16, 32, 64 or 128"); return 4; }
   if (act_dt == BF16)
     hipLaunchKernelGGL(ln_mod_fwd_k<uint16_t>, dim3(nrows), dim3(256), 0, s, (const uint16_t*)x, D, rm, row0,
                        mod_txt, mod_img, mod_w, sh_off, sc_off, (uint16_t*)a, mean, rstd);
@@ -658,12 +656,12 @@ int ln_mod_fwd(const void* x, int act_dt, int D, RowMap rm, int row0, int nrows,
   return 0;
 }
 
-template <typename T, typename TG>
+template <typename T>
 __global__ __launch_bounds__(256) void ln_mod_bwd_k(const float* __restrict__ dA, const T* __restrict__ x, int D,
                                                     Chunks ch, int c0, const float* __restrict__ mean,
                                                     const float* __restrict__ rstd, const float* __restrict__ mt,
                                                     const float* __restrict__ mi, int mod_w, int sc_off,
-                                                    const TG* gin, float* g, float* __restrict__ psc,
+                                                    const float* gin, float* g, float* __restrict__ psc,
                                                     float* __restrict__ psh) {
   __shared__ float sh[16];
   const int q = c0 + blockIdx.x;
@@ -704,7 +702,7 @@ __global__ __launch_bounds__(256) void ln_mod_bwd_k(const float* __restrict__ dA
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
       const int c = threadIdx.x + i * 256;
-      if (c < D) g[(size_t)r * D + c] = ldf(gin, (size_t)r * D + c) + rs * (dxh[i] - m1 - xh[i] * m2);
+      if (c < D) g[(size_t)r * D + c] = gin[(size_t)r * D + c] + rs * (dxh[i] - m1 - xh[i] * m2);
     }
   }
 #pragma unroll
@@ -869,12 +867,13 @@ int ln_mod_bwd(const float* dA, const void* x, int act_dt, int D, RowMap rm, int
     LAUNCH_OK("ln_mod_bwd_vec");
     return 0;
   }
-#define LNK(T, TG)                                                                                              \
-  hipLaunchKernelGGL((ln_mod_bwd_k<T, TG>), dim3(nc), dim3(256), 0, s, dA, (const T*)x, D, ch, c0, mean, rstd, \
-                     mod_txt, mod_img, mod_w, sc_off, (const TG*)g_in, g, part_scale, part_shift)
-  if (act_dt == BF16 && g_in_dt == BF16) LNK(uint16_t, uint16_t);
-  else if (act_dt == BF16) LNK(uint16_t, float);
-  else LNK(float, float);
+  // (the final LayerNorm of a network without blocks, as in the forward)
+  if (g_in_dt != F32) { set_error("ln_mod_bwd: unaligned operands of a bf16 incoming gradient"); return 1; }
+#define LNK(T)                                                                                                \
+  hipLaunchKernelGGL((ln_mod_bwd_k<T>), dim3(nc), dim3(256), 0, s, dA, (const T*)x, D, ch, c0, mean, rstd, \
+                     mod_txt, mod_img, mod_w, sc_off, (const float*)g_in, g, part_scale, part_shift)
+  if (act_dt == BF16) LNK(uint16_t);
+  else LNK(float);
 #undef LNK
   LAUNCH_OK("ln_mod_bwd");
   return 0;
@@ -946,19 +945,20 @@ int gated_residual(const void* xi, const void* y, int act_dt, int D, int ld_y, R
 int gated_residual_ln(const void* xi, const void* y, int act_dt, int D, int ld_y, RowMap rm, int row0, int nrows,
                       const float* mod_txt, const float* mod_img, int mod_w, int gate_off, void* xo, int sh_off,
                       int sc_off, void* a, float* mean, float* rstd, hipStream_t s) {
-  if (nrows > 0 && D <= 256 * MAXC && ln_vec(xi, D, mod_txt, mod_img, mod_w, sh_off, sc_off, a) && ld_y % 8 == 0 &&
-      al16(y) && al16(xo) && gate_off % 4 == 0) {
-    if (act_dt == BF16)
-      ln_fwd_vec<uint16_t, LN_GATED>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
-                                 {(const uint16_t*)y, (uint16_t*)xo, ld_y, gate_off}, s);
-    else
-      ln_fwd_vec<float, LN_GATED>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
-                              {(const float*)y, (float*)xo, ld_y, gate_off}, s);
-    LAUNCH_OK("gated_residual_ln");
-    return 0;
+  if (nrows <= 0) return 0;
+  if (D > 256 * MAXC || !ln_vec(xi, D, mod_txt, mod_img, mod_w, sh_off, sc_off, a) || ld_y % 8 || !al16(y) ||
+      !al16(xo) || gate_off % 4) {
+    set_error("gated_residual_ln: hidden above 4096 or unaligned operands");
+    return 1;
   }
-  if (int rc = gated_residual(xi, y, act_dt, D, ld_y, rm, row0, nrows, mod_txt, mod_img, mod_w, gate_off, xo, s)) return rc;
-  return ln_mod_fwd(xo, act_dt, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd, s);
+  if (act_dt == BF16)
+    ln_fwd_vec<uint16_t, LN_GATED>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
+                                   {(const uint16_t*)y, (uint16_t*)xo, ld_y, gate_off}, s);
+  else
+    ln_fwd_vec<float, LN_GATED>(xi, D, rm, row0, nrows, mod_txt, mod_img, mod_w, sh_off, sc_off, a, mean, rstd,
+                                {(const float*)y, (float*)xo, ld_y, gate_off}, s);
+  LAUNCH_OK("gated_residual_ln");
+  return 0;
 }
 
 template <typename T, typename TG>

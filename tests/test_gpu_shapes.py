@@ -153,3 +153,17 @@ def test_norm_widths(heads, head_dim, act):
 def test_mlp_widths_of_a_single_block(heads, head_dim, act):
     check_pass(block(heads, head_dim, 9, 4, 6, act=act, block_only=0, n_single=1, mlp_hidden=170), 1, 2,
                2e-2 if act == pk.BF16 else 1e-4)
+
+
+# hidden sizes that are not multiples of 8: a network without blocks (its final LayerNorm on the element-wise kernels;
+# the text embedding then has no gradient), and with blocks refused for their head dim
+@pytest.mark.parametrize("act", [pk.F32, pk.BF16])
+def test_hidden_sizes_without_attention(act):
+    none = dict(n_double=0, block_only=0, in_ch=3, patch=1, txt_dim=20)
+    check_pass(block(5, 4, 9, 4, 6, act=act, **none), 2, 2, 2e-2 if act == pk.BF16 else 1e-4)
+    check_pass(block(3, 100, 2, 5, 7, act=act, **none), 1, 2, 2e-2 if act == pk.BF16 else 1e-4)
+    for over in (dict(), dict(block_only=0)):
+        for heads, head_dim in ((5, 4), (2, 20)):
+            with pytest.raises(pk.api.JaggError, match="head_dim must be 16, 32, 64 or 128") as e:
+                Case(block(heads, head_dim, 9, 4, 6, act=act, **over), B=1, W=2).saved_pair()
+            assert e.value.status == 4
