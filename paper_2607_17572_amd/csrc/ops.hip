@@ -307,9 +307,10 @@ static int sl_parts(int cpt, int Din, int Dout, int np) {
 // these the size grows with the batch.
 size_t small_linear_bwd_part_floats(int B, int Din, int Dout, int np) {
   size_t most = 0;
-  for (const int b : {std::min(B, 4), std::min(B, 8), B})
+  for (const int b : {4, 8, B})
     // rows that are not aligned for the vector kernel take one column per thread
-    most = std::max(most, (size_t)np * std::max(sl_parts(sl_cpt(b), Din, Dout, np), sl_parts(1, Din, Dout, np)) * b * Din);
+    if (b <= B)
+      most = std::max(most, (size_t)np * std::max(sl_parts(sl_cpt(b), Din, Dout, np), sl_parts(1, Din, Dout, np)) * b * Din);
   return most;
 }
 
