@@ -162,7 +162,7 @@ struct Saved {
   std::vector<SglAct> s;
 };
 
-static void plan_dbl(const Model& m, Arena& a, int B, DblAct& A, bool full) {
+static void plan_dbl(const Model& m, Arena& a, int B, DblAct& A, bool full, bool out = true) {
   const size_t rows = (size_t)B * m.N, es = dsize(m.act);
   const size_t hn = (size_t)B * m.H * m.N;
   if (full) {
@@ -183,7 +183,7 @@ static void plan_dbl(const Model& m, Arena& a, int B, DblAct& A, bool full) {
     A.h = a.take(rows * m.F * es);
     A.y2 = a.take(rows * m.D * es);
   }
-  A.x_out = a.take(rows * m.D * es);
+  if (out) A.x_out = a.take(rows * m.D * es);
 }
 
 static void plan_sgl(const Model& m, Arena& a, int B, SglAct& A, bool full) {
@@ -221,7 +221,12 @@ static size_t plan_saved(const Model& m, int B, void* base, Saved& S) {
   S.d.resize(m.c.n_double);
   S.s.resize(m.c.n_single);
   void* prev = S.g.x0;
-  for (auto& A : S.d) { plan_dbl(m, a, B, A, full); A.x_in = prev; prev = A.x_out; }
+  for (auto& A : S.d) {
+    // the last block of a block-only model writes the caller's output
+    plan_dbl(m, a, B, A, full, !m.c.block_only || &A != &S.d.back());
+    A.x_in = prev;
+    prev = A.x_out;
+  }
   for (auto& A : S.s) { plan_sgl(m, a, B, A, full); A.x_in = prev; prev = A.x_out; }
   if (!m.c.block_only) {
     S.g.fmod = a.f32((size_t)B * 2 * m.D);

@@ -332,3 +332,20 @@ def test_workspace_is_linear_in_the_tokens(act, head_dim):
         size.append(n.value)
         L.jagg_ctx_destroy(h)
     assert size[1] <= 4.01 * size[0], size
+
+
+# What a checkpointed block-only model keeps: the time embedding's vectors and every block's input rows, each at a
+# multiple of 256 bytes; the last block's output is the caller's
+@pytest.mark.parametrize("n_double", [1, 3])
+@pytest.mark.parametrize("act", [pk.F32, pk.BF16])
+def test_saved_bytes_of_a_checkpointed_block_model(n_double, act):
+    L = _lib_or_skip()
+    c = pk.Config(n_double=n_double, n_single=0, hidden=192, heads=3, head_dim=64, mlp_hidden=768, in_ch=16, patch=2,
+                  lat_h=10, lat_w=14, n_txt=9, txt_dim=64, t_freq_dim=250, block_only=1, act_dtype=act, checkpoint=1)
+    h, n = ctypes.c_void_p(), ctypes.c_size_t()
+    assert L.jagg_ctx_create(ctypes.byref(c.c()), None, ctypes.byref(h)) == 0
+    for B in (1, 5):
+        assert L.dit_saved_bytes(h, B, ctypes.byref(n)) == 0
+        sizes = [4 * B * 250] + 4 * [4 * B * 192] + n_double * [B * c.n_tok * 192 * (2 if act == pk.BF16 else 4)]
+        assert n.value == sum(-(-x // 256) * 256 for x in sizes)
+    L.jagg_ctx_destroy(h)
