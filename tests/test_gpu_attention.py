@@ -55,7 +55,7 @@ def run(dt, Dh, B, H, nt, ni, extra=0):
     """{name: (kernel's result, fp64 result)}; extra: columns of the rows of O beyond the heads'"""
     N, ld = nt + ni, H * Dh + extra
     g = torch.Generator(device="cuda").manual_seed(100 * Dh + N)
-    q, k, v, do = (torch.randn((B, H, N, Dh), generator=g, device="cuda").to(dt) for _ in range(4))
+    q, k, v, do = (torch.randn((B, H, N, Dh), generator=g, device="cuda", dtype=torch.float32).to(dt) for _ in range(4))
     q64, k64, v64, do64 = (x.double() for x in (q, k, v, do))
     s = torch.stack([torch.stack([q64[b, h] @ k64[b, h].t().contiguous() for h in range(H)]) for b in range(B)]) / math.sqrt(Dh)
     lse64 = torch.logsumexp(s, -1)
@@ -66,7 +66,7 @@ def run(dt, Dh, B, H, nt, ni, extra=0):
     rows, code = rows_of_tokens(B, nt, ni), pk.BF16 if dt == torch.bfloat16 else pk.F32
     rm = RowMap(B, nt, ni)
     O = torch.full((B * N, ld), float("nan"), dtype=dt, device="cuda")
-    lse = torch.empty((B, H, N), device="cuda")
+    lse = torch.empty((B, H, N), device="cuda", dtype=torch.float32)
     call("fwd", Fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), O.data_ptr(), ld, lse.data_ptr(), B, H, N, Dh, code, rm))
     out = {"O": (O[rows][..., :H * Dh].reshape(B, N, H, Dh).permute(0, 2, 1, 3), o64), "lse": (lse, lse64)}
     # the backward from the stored O and log-sum-exp, as the pass has them
@@ -76,7 +76,7 @@ def run(dt, Dh, B, H, nt, ni, extra=0):
     ref = {"dQ": mm(ds, k64), "dK": mm(t(ds), q64), "dV": mm(t(p), do64)}
     got = {n: torch.full_like(q, float("nan")) for n in ref}
     Or, dOr = token_major(o, rows, ld), token_major(do, rows, H * Dh)
-    delta = torch.empty((2, B, H, N), device="cuda")
+    delta = torch.empty((2, B, H, N), device="cuda", dtype=torch.float32)
     call("bwd", Bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), Or.data_ptr(), ld, dOr.data_ptr(), H * Dh,
                     lse32.data_ptr(), delta.data_ptr(), got["dQ"].data_ptr(), got["dK"].data_ptr(),
                     got["dV"].data_ptr(), code, B, H, N, Dh, code, rm, None, 0, 0))
