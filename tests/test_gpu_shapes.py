@@ -69,13 +69,18 @@ def test_bf16_product_tiles(rows, n_out, n_in):
     dX = torch.empty(rows, n_in, dtype=torch.float32, device="cuda")
     dYd, Xd, Wd = (to_dev(x, torch.bfloat16) for x in (dY, X, W))
     ctx.linear_grad(pk.DGRAD, dYd, Wd, dX)
-    # the row past the last one of X and dY must not reach the sums: rows of a larger allocation, the rest NaN
-    big = torch.full((rows + 64, n_in), float("nan"), dtype=torch.bfloat16, device="cuda")
-    big[:rows] = Xd
+    # rows past the last one of X and of dY must not reach the sums: each the first rows of a larger allocation, the
+    # rest NaN (both, since a NaN of one times a zero read for the other shows, and a finite value would not)
+    def within_nan(x):
+        big = torch.full((rows + 64, x.shape[1]), float("nan"), dtype=torch.bfloat16, device="cuda")
+        big[:rows] = x
+        return big[:rows]
+
+    dYn, Xn = within_nan(dYd), within_nan(Xd)
     dW = torch.ones(n_out, n_in, dtype=torch.float32, device="cuda")
-    ctx.linear_grad(pk.WGRAD, dYd, big[:rows], dW, beta=1.0)
+    ctx.linear_grad(pk.WGRAD, dYn, Xn, dW, beta=1.0)
     dWb = torch.ones(n_out, n_in, dtype=torch.bfloat16, device="cuda")
-    ctx.linear_grad(pk.WGRAD, dYd, big[:rows], dWb, beta=1.0)
+    ctx.linear_grad(pk.WGRAD, dYn, Xn, dWb, beta=1.0)
     want = 1.0 + mmdit.wgrad(dY, X)
     # fp32 sums of exact products (K <= 2500: below 1e-5); one bf16 rounding is 2^-9 at most
     assert rel_l2(dX.double().cpu().numpy(), dY @ W) <= 1e-5
