@@ -92,8 +92,9 @@ jagg_status dit_param_layout(const dit_config* cfg, size_t* n_tensors, size_t* n
 
 /* Create a context bound to `hip_stream` (a hipStream_t, or NULL for the null
  * stream) on the current device.  Validates the config.  Host only.  On its
- * first backward the context creates one more stream of its own (default
- * priority) for the double blocks' weight-gradient products; that work is
+ * first backward of more than 3 million elements (token rows x hidden) the
+ * context creates one more stream of its own (default priority) for the double
+ * blocks' weight-gradient products and column reductions; that work is
  * forked from and joined back into `hip_stream` with events inside each call,
  * so every call stays ordered on `hip_stream` alone. */
 jagg_status jagg_ctx_create(const dit_config* cfg, void* hip_stream, jagg_ctx** out);
@@ -101,7 +102,8 @@ jagg_status jagg_ctx_create(const dit_config* cfg, void* hip_stream, jagg_ctx** 
 void jagg_ctx_destroy(jagg_ctx* ctx);
 
 /* Bytes of the saved-activation buffer for a forward of `batch` samples, and
- * of the workspace needed by any call on `batch` samples.  Host only. */
+ * of the workspace needed by any call on `batch` samples.  Neither shrinks as
+ * the batch grows: a workspace serves every smaller batch too.  Host only. */
 jagg_status dit_saved_bytes(const jagg_ctx* ctx, int batch, size_t* bytes);
 jagg_status dit_workspace_bytes(const jagg_ctx* ctx, int batch, size_t* bytes);
 /* Bind a caller-owned device workspace (kept until replaced or the context is

@@ -28,7 +28,7 @@ struct AttnBwd {
   void* dQ; void* dK; void* dV; int dt_d;
   int B, H, N, Dh, dt;
   RowMap rm;
-  // bf16 MFMA path: the dK/dV kernel stores dS^T here and dQ = dS K is
+  // bf16 MFMA path, head dim 128: the dK/dV kernel stores dS^T here and dQ = dS K is
   // formed from it without recomputing the scores (nullptr: the dQ kernel
   // recomputes them).  nk_pad x ld_ds elements per (sample, head), in chunks
   // of 128 keys x 64 queries (16 KB, key rows of 64 queries): element
@@ -41,7 +41,7 @@ struct AttnBwd {
   int ld_ds = 0, nk_pad = 0;
 };
 int attention_bwd(const AttnBwd& a, hipStream_t s);
-// Padded dS^T geometry of the bf16 MFMA path: rows (keys) and columns
+// Padded dS^T geometry of that path: rows (keys) and columns
 // (queries) to multiples of 128 (the key block of the dK/dV kernel and the
 // query block of the dQ kernel).
 inline int attn_ds_rows(int N) { return (N + 127) / 128 * 128; }
