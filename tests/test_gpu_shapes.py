@@ -56,8 +56,7 @@ def test_unaligned_bf16_products():
     assert rel_l2(dW.double().cpu().numpy(), 1.0 + mmdit.wgrad(dY, X)) <= 1e-5
 
 
-# bf16 products of 64 x 64 and 128 x 128 direct-to-LDS tiles and 128 x 128 register-staged ones: one row below, at and
-# above a tile edge, one k tile, ragged k in the weight gradient (rows), K = 96 (not a multiple of 64), an odd number of
+# bf16 products of 64 x 64 and 128 x 128 direct-to-LDS tiles: one row below and above a tile edge, one k tile, ragged k in the weight gradient (rows), K = 96 (not a multiple of 64), an odd number of
 # k tiles over two k groups (1057 rows: 34 with a ragged last one; K = 1056: 33)
 @pytest.mark.parametrize("rows,n_out,n_in", [(8, 64, 64), (63, 96, 72), (65, 64, 136), (129, 768, 200), (1057, 72, 96), (200, 1056, 136), (127, 2048, 1024),
                                              (1089, 1536, 768), (2500, 1544, 1536)])
@@ -90,9 +89,13 @@ def test_bf16_product_tiles(rows, n_out, n_in):
 
 @pytest.mark.parametrize("c,B", [
     (block(6, 128, 77, 10, 14, act=pk.BF16), 1),   # 64 x 64 tiles
-    (block(6, 128, 77, 34, 38, act=pk.BF16, block_only=0, n_single=1), 2),   # 128 x 128 and 64 x 64
+    # 128 x 128 (register-staged in the forward) and 64 x 64
+    (block(6, 128, 77, 34, 38, act=pk.BF16, block_only=0, n_single=1), 2),
     (block(3, 32, 9, 6, 6, act=pk.BF16), 1),  # K = 96 and 288
-], ids=["tiles64", "tiles128", "k96"])
+    # forward products on 128 x 128 direct-to-LDS tiles: K = 480 is not a multiple of 64, 168 to 351 tiles with all
+    # three epilogues (bias; bias + GELU; both in one launch for the single block)
+    (block(15, 32, 77, 34, 38, act=pk.BF16, block_only=0, n_single=1), 2),
+], ids=["tiles64", "tiles128", "k96", "k480"])
 def test_bf16_products_of_a_pass(c, B):
     check_pass(c, B, 3, 2e-2)
 
